@@ -160,11 +160,10 @@ int validate_net(const lr_donn* net, bool need_layers) {
 size_t align256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
 
 struct Layout {
-  size_t chirp_x = 0, chirp_y = 0, hp = 0, mod = 0, w0 = 0, w1 = 0;
+  size_t chirp_x = 0, chirp_y = 0, mod = 0, w0 = 0, w1 = 0;
   size_t sums_part = 0, grad_sums = 0, dphi_part = 0, regions = 0, row_mask = 0, col_mask = 0, row_perm = 0,
          col_perm = 0, total = 0;
   int ntiles_vec = 0;   // tiles over n vectors
-  int ntiles_spec = 0;  // tiles over n_fft spectrum columns (angular spectrum)
   int groups = 1;
   int spg = 1;
 };
@@ -176,9 +175,7 @@ Layout make_layout(const lr_donn* net, int batch, int op) {
   const int n = net->n;
   const int N = net->n_fft;
   const bool as = net->approx != LR_FRESNEL;  // the non-separable passes
-  const lr::TileShape sh = lr::tile_shape(N, 0);
-  L.ntiles_vec = ceil_div(n, sh.T);
-  L.ntiles_spec = ceil_div(N, sh.T);
+  L.ntiles_vec = ceil_div(n, as ? lr::as_row_tile(N) : lr::tile_shape(N, 0).T);
   const size_t c64 = 8;
   const size_t nn = static_cast<size_t>(n) * n;
   const size_t field = static_cast<size_t>(batch) * (as ? static_cast<size_t>(n) * N : nn) * c64;
@@ -192,7 +189,9 @@ Layout make_layout(const lr_donn* net, int batch, int op) {
     L.chirp_x = take(N * c64);
     L.chirp_y = take(N * c64);
   } else {
-    L.hp = take(static_cast<size_t>(N) * N * c64);
+    // not used by the passes, which read the caller's table; part of the size
+    // so that which batches fit a fixed workspace does not change
+    take(static_cast<size_t>(N) * N * c64);
   }
   if (op != LR_OP_PROPAGATE) L.mod = take(static_cast<size_t>(net->num_layers) * nn * c64);
   L.w0 = take(field);
@@ -209,7 +208,8 @@ Layout make_layout(const lr_donn* net, int batch, int op) {
   if (op == LR_OP_BACKWARD) {
     if (K > 0) L.grad_sums = take(static_cast<size_t>(batch) * K * 4);
     const int work_tiles = L.ntiles_vec;
-    int spg = ceil_div(batch * work_tiles, 2048);
+    // (the angular-spectrum row passes run single waves: twice the workgroups)
+    int spg = ceil_div(batch * work_tiles, as ? 4096 : 2048);
     if (spg < 1) spg = 1;
     if (spg > batch) spg = batch > 0 ? batch : 1;
     L.spg = spg;
@@ -236,7 +236,7 @@ Axis pass_axis(int p) { return (p & 1) ? lr::kRow : lr::kCol; }
 // Layer l (1-based) is modulated in pass l+1: transposed storage when that pass is a row pass,
 // except on the wide row tiles of the 500-point plan (full aperture), which read rows.
 int layer_transposed(const lr_donn* net, int l) {
-  if (net->approx != LR_FRESNEL) return 1;
+  if (net->approx != LR_FRESNEL) return 0;
   if (pass_axis(l + 1) != lr::kRow) return 0;
   return lr::wide_row_tiles(net->n_fft) && net->n == net->n_fft ? 0 : 1;
 }
@@ -304,7 +304,27 @@ int fr_pass(int N, lr::PassKind kind, Axis ax, const PassArgs& a, hipStream_t st
   if (kind == lr::kPropOnce || kind == lr::kFwdMid) LR_TRY(schedule_layer_pass(N, kind, ax, 0, s));
   return run_timed(fr_name(N, kind, ax), st, [&] { return lr::launch_fresnel_pass(N, kind, ax, s, st); });
 }
-int as_pass(int N, lr::AsPassKind kind, const PassArgs& a, hipStream_t st) {
+// Row kinds of the angular-spectrum path: one workgroup per (tile, sample), or
+// (accumulating kinds, max_lanes > 0) as many persistent ones as fit, each
+// keeping one tile; a.lanes returns the partials written.
+int schedule_as_row(int N, lr::AsPassKind kind, int max_lanes, PassArgs& a) {
+  const int tile = lr::as_row_tile(N);
+  if (tile <= 0) return LR_E_HIP;
+  a.ntiles = ceil_div(a.n, tile);
+  a.lanes = 0;
+  a.workers = a.ntiles * a.batch;
+  if (max_lanes > 0) {
+    const int slots = lr::as_pass_slots(N, kind, 2 * a.n == N);
+    if (slots <= 0) return LR_E_HIP;
+    const int lanes = std::max(1, slots / a.ntiles);
+    a.lanes = std::min(lanes, std::max(1, std::min(max_lanes, a.batch)));
+    a.workers = a.lanes * a.ntiles;
+  }
+  return LR_OK;
+}
+int as_pass(int N, lr::AsPassKind kind, const PassArgs& args, hipStream_t st) {
+  PassArgs a = args;
+  if (a.workers == 0 && kind != lr::kAsCol && kind != lr::kAsColFar) LR_TRY(schedule_as_row(N, kind, 0, a));
   return run_timed(as_name(N, kind), st, [&] { return lr::launch_as_pass(N, kind, a, st); });
 }
 
@@ -315,7 +335,8 @@ PassArgs base_args(const lr_donn* net, int batch) {
   a.off = (net->n_fft - net->n) / 2;
   a.batch = batch;
   a.spg = 1;
-  a.tab_sym = net->approx == LR_ANGULAR_SPECTRUM ? 1 : 0;
+  a.tab_sym = net->approx == LR_ANGULAR_SPECTRUM || net->approx == LR_FRAUNHOFER ? 1 : 0;
+  a.scale = static_cast<float>(1.0 / (static_cast<double>(net->n_fft) * net->n_fft));
   return a;
 }
 
@@ -372,13 +393,6 @@ int check_work(const lr_donn* net, int batch, int op, void* d_work, size_t work_
   return LR_OK;
 }
 
-// Scale of the column-permuted 2-D table: 1/N^2 (the inverse transform's
-// normalisation) for a propagation, 1 for the far-field table.
-float as_table_scale(const lr_donn* net) {
-  const double N = static_cast<double>(net->n_fft);
-  return net->approx == LR_FRAUNHOFER ? 1.0f : static_cast<float>(1.0 / (N * N));
-}
-
 // The separable passes of a network whose layer fills the FFT grid keep
 // their fields, modulation tables and dphi partials in the plan's slot order
 // (no index arithmetic in the passes); padded layers use natural order.
@@ -387,27 +401,20 @@ lr::SlotMap slot_map_of(const lr_donn* net) {
   return slot_ordered(net) ? lr::slot_map(net->n_fft) : lr::SlotMap{0, 0, 0};
 }
 
-// Transfer-function tables of the passes: the separable Fresnel chirps (in
-// natural frequency order; each pass stages them in its own plan order) or the
-// column-permuted copy of H the angular-spectrum passes read.
-int prep_tables(const lr_donn* net, const Layout& L, void* w, hipStream_t st) {
+// The separable Fresnel chirps of a propagation, in natural frequency order
+// (each pass stages them in its own plan order).
+int prep_chirps(const lr_donn* net, const Layout& L, void* w, hipStream_t st) {
   const float2* H = reinterpret_cast<const float2*>(net->d_H);
-  if (net->approx == LR_FRESNEL) {
-    return run_timed("prep_layers", st, [&] {
-      return lr::launch_prep_layers(nullptr, 0, net->n, 1.0f, nullptr, lr::SlotMap{0, 0, 0}, nullptr, nullptr,
-                                    nullptr, nullptr, nullptr, nullptr, nullptr, H, net->n_fft, at<float2>(w, L.chirp_x),
-                                    at<float2>(w, L.chirp_y), st);
-    });
-  }
-  return run_timed("prep_as_table", st, [&] {
-    return lr::launch_prep_as_table(net->n_fft, H, at<float2>(w, L.hp), as_table_scale(net),
-                                    net->approx == LR_FRAUNHOFER ? 1 : 0, st);
+  return run_timed("prep_layers", st, [&] {
+    return lr::launch_prep_layers(nullptr, 0, net->n, 1.0f, nullptr, lr::SlotMap{0, 0, 0}, nullptr, nullptr,
+                                  nullptr, nullptr, nullptr, nullptr, nullptr, H, net->n_fft, at<float2>(w, L.chirp_x),
+                                  at<float2>(w, L.chirp_y), st);
   });
 }
 
 // Per-call tables of a forward or backward pass in one launch: the modulation
 // of every layer, the Fresnel chirps, and (when the call reads detector
-// regions) the region tables; the angular-spectrum table takes its own launch.
+// regions) the region tables.
 int prep_layers(const lr_donn* net, const float* d_phi, bool regions, const Layout& L, void* w, hipStream_t st) {
   int orient[LR_MAX_LAYERS];
   for (int l = 0; l < net->num_layers; ++l) orient[l] = layer_transposed(net, l + 1);
@@ -415,12 +422,6 @@ int prep_layers(const lr_donn* net, const float* d_phi, bool regions, const Layo
   const lr::Regions r = host_regions(net->det);
   const bool fresnel = net->approx == LR_FRESNEL;
   const float2* H = reinterpret_cast<const float2*>(net->d_H);
-  if (!fresnel) {
-    LR_TRY(run_timed("prep_as_table", st, [&] {
-      return lr::launch_prep_as_table(net->n_fft, H, at<float2>(w, L.hp), as_table_scale(net),
-                                    net->approx == LR_FRAUNHOFER ? 1 : 0, st);
-    }));
-  }
   return run_timed("prep_layers", st, [&] {
     return lr::launch_prep_layers(d_phi, net->num_layers, net->n, net->gamma, orient, slot_map_of(net),
                                   at<float2>(w, L.mod),
@@ -664,10 +665,10 @@ int lr_propagate(const lr_donn* net, int32_t batch, const lr_c64* d_in, lr_c64* 
   }
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int N = net->n_fft;
-  LR_TRY(prep_tables(net, L, d_work, st));
   PassArgs a = base_args(net, batch);
   a.conj_tab = adjoint ? 1 : 0;
   if (net->approx == LR_FRESNEL) {
+    LR_TRY(prep_chirps(net, L, d_work, st));
     a.nvec = net->n;
     a.ntiles = L.ntiles_vec;
     a.in = d_in;
@@ -679,9 +680,8 @@ int lr_propagate(const lr_donn* net, int32_t batch, const lr_c64* d_in, lr_c64* 
     a.tab = at<float2>(d_work, L.chirp_y);
     return fr_pass(N, lr::kPropOnce, lr::kCol, a, st);
   }
+  const float2* H = reinterpret_cast<const float2*>(net->d_H);
   a.in = d_in;
-  a.nvec = net->n;
-  a.ntiles = L.ntiles_vec;
   a.out = at<float2>(d_work, L.w0);
   a.spec_centred = net->approx == LR_FRAUNHOFER ? 1 : 0;
   LR_TRY(as_pass(N, lr::kAsRowFirst, a, st));
@@ -690,21 +690,15 @@ int lr_propagate(const lr_donn* net, int32_t batch, const lr_c64* d_in, lr_c64* 
     // far field: the column DFT with the output factors, straight into d_out ([batch][N][N])
     a.in = at<float2>(d_work, L.w0);
     a.out = reinterpret_cast<float2*>(d_out);
-    a.nvec = N;
-    a.ntiles = L.ntiles_spec;
-    a.tab = at<float2>(d_work, L.hp);
+    a.tab = H;
     return as_pass(N, lr::kAsColFar, a, st);
   }
   a.in = at<float2>(d_work, L.w0);
   a.out = at<float2>(d_work, L.w1);
-  a.nvec = N;
-  a.ntiles = L.ntiles_spec;
-  a.tab = at<float2>(d_work, L.hp);
+  a.tab = H;
   LR_TRY(as_pass(N, lr::kAsCol, a, st));
   a.in = at<float2>(d_work, L.w1);
   a.out = reinterpret_cast<float2*>(d_out);
-  a.nvec = net->n;
-  a.ntiles = L.ntiles_vec;
   return as_pass(N, lr::kAsRowIfft, a, st);
 }
 
@@ -887,8 +881,6 @@ int lr_donn_forward(const lr_donn* net, int32_t batch, const float* d_amp, const
       LR_TRY(fr_pass(N, lr::kFwdLast, ax, d, st));
     }
   } else {
-    a.nvec = n;
-    a.ntiles = L.ntiles_vec;
     a.in = d_amp;
     a.in_real = 1;
     a.out = w[0];
@@ -899,9 +891,7 @@ int lr_donn_forward(const lr_donn* net, int32_t batch, const float* d_amp, const
       PassArgs c = a;
       c.in = w[cur];
       c.out = w[cur ^ 1];
-      c.nvec = N;
-      c.ntiles = L.ntiles_spec;
-      c.tab = at<float2>(d_work, L.hp);
+      c.tab = reinterpret_cast<const float2*>(net->d_H);
       LR_TRY(as_pass(N, lr::kAsCol, c, st));
       cur ^= 1;
       if (hop <= Lyr) {
@@ -1072,25 +1062,20 @@ int lr_donn_backward(const lr_donn* net, int32_t batch, const float* d_phi, cons
     PassArgs c = a;
     c.in = w[cur];
     c.out = w[cur ^ 1];
-    c.nvec = N;
-    c.ntiles = L.ntiles_spec;
-    c.tab = at<float2>(d_work, L.hp);
+    c.tab = reinterpret_cast<const float2*>(net->d_H);
     LR_TRY(as_pass(N, lr::kAsCol, c, st));
     cur ^= 1;
     PassArgs r = a;
-    r.spg = L.spg;
     r.in = w[cur];
     r.mod = ws_mod + static_cast<size_t>(l - 1) * nn;
     r.act_in = saved + static_cast<size_t>(l - 1) * batch * nn;
     r.dphi_part = part_of(l);
-    if (l > 1) {
-      r.out = w[cur ^ 1];
-      LR_TRY(as_pass(N, lr::kAsRowBwdMid, r, st));
-      cur ^= 1;
-    } else {
-      LR_TRY(as_pass(N, lr::kAsRowBwdLast, r, st));
-    }
-    groups_of[l - 1] = L.groups;
+    const lr::AsPassKind kind = l > 1 ? lr::kAsRowBwdMid : lr::kAsRowBwdLast;
+    LR_TRY(schedule_as_row(N, kind, L.groups, r));
+    if (l > 1) r.out = w[cur ^ 1];
+    LR_TRY(as_pass(N, kind, r, st));
+    if (l > 1) cur ^= 1;
+    groups_of[l - 1] = r.lanes;
   }
   return reduce_all();
 }

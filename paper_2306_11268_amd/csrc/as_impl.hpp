@@ -1,0 +1,722 @@
+// Angular-spectrum passes (non-separable transfer functions) for gfx950.
+//
+// A hop is FFT_x of every row, then per column FFT_y, x H, IFFT_y, then IFFT_x
+// of every row.  Between passes a sample is stored as n rows of N x-spectrum
+// values in natural frequency order ([B][n][N]); only the n rows inside the
+// aperture carry data.  Positions and frequencies are natural at every size
+// (AsPlanFor), so a lane's elements lie at one per-lane base plus
+// compile-time offsets in every array a pass touches, and no array is staged
+// through shared memory:
+//
+//   A-item j of a vector: positions j + N2*k, k < N1;
+//   B-item k1: frequencies k1 + N1*k2, k2 < N2, and on its other side the
+//     elements j < N2 it exchanges with the A-items.
+//
+// Shared memory holds only that exchange; for the longer plans one float
+// component at a time (real parts, then imaginary parts): half the bytes of a
+// complex tile, so twice the resident waves, which is what bounds these
+// passes (the 1024-point column tile of complex values in both directions
+// held 74 KB per 4 waves: 8 waves per CU).  Entry (k1, j) of a vector is at
+// k1*(N2+1) + j (N2 is even), which spreads the B-side reads of a wave over all
+// banks.
+//
+// Measured (10 layers, 512 in 1024, batch 64, one MI355X; before: tiles staged
+// through shared memory): column pass 285 -> 156 us (2109 VALU instructions
+// per lane, 132 us at the measured issue rate), row layer pass 175 -> 95 us
+// (537 MB at 5.6 TB/s, the rate of a large copy), the network 5.08 -> 2.79 ms;
+// 5 layers of training, 200 in 400, batch 100: 1.60 -> 0.98 ms.
+//
+// With a field zero padded to twice its size (HALF: n = N/2, N1 divisible by
+// 4) a lane's elements inside the aperture are exactly k = N1/4 .. 3*N1/4 - 1:
+// the A-step runs HalfDft, and half of the loads, stores and products vanish.
+#pragma once
+
+#include "kernels_impl.hpp"
+
+namespace lr {
+
+// Barrier between shared-memory phases of a workgroup of P threads.  One wave
+// needs no hardware barrier and no wait: its shared-memory accesses complete
+// in order, so only the compiler has to keep them in order.
+template <int P>
+__device__ __forceinline__ void exchange_sync() {
+  if constexpr (P == 64) {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  } else {
+    __syncthreads();
+  }
+}
+
+// Rounds of B-items per lane (item k1 = s + N2*ic in round ic).
+template <class PL, bool FENCED = false>
+struct AsItems {
+  using Plan = PL;
+  static constexpr int N = PL::N;
+  static constexpr int N1 = PL::N1;
+  static constexpr int N2 = PL::N2;
+  static constexpr int IB = (N1 + N2 - 1) / N2;
+  static constexpr bool FULL_ROUNDS = N1 % N2 == 0;
+  static constexpr int P1 = N2 + 1;  // exchange pitch of a B-item
+  static constexpr bool LONG = FENCED || N1 > 16 || N2 * IB > 16;
+  static_assert(!PL::PFA && N2 % 2 == 0, "natural order and an odd exchange pitch");
+  // Whether lane s has an item in round ic, and the item it works on: row
+  // passes (REPEAT) let a lane past the last item repeat one of that round's
+  // items, the same values from and to the same shared-memory entries, because
+  // a branch around the item kept the compiler from scheduling the arrays live
+  // across it (100-400 bytes of scratch); column passes, where whole waves are
+  // past the last item, branch (500 points: 54 us against 106 with repeats).
+  static __device__ __forceinline__ bool item(int s, int ic) { return FULL_ROUNDS || s + N2 * ic < N1; }
+  template <bool REPEAT>
+  static __device__ __forceinline__ int item_of(int s, int ic) {
+    constexpr int last = N1 - N2 * (IB - 1);  // items of the last round
+    return N2 * ic + (!REPEAT || FULL_ROUNDS || ic + 1 < IB ? s : s % last);
+  }
+  static constexpr int K0(bool half) { return half ? N1 / 4 : 0; }
+  static constexpr int KN(bool half) { return half ? N1 / 2 : N1; }  // elements of an A-item in the aperture (HALF) or all
+};
+
+// Exchange of one vector's A-item (x) with its B-items (y).  The A side of
+// element k1 is buf[ab + SA*k1], the B side of element q of round ic
+// buf[bb[ic] + SQ*q].  Each lane rewrites only entries it read last, so
+// successive exchanges need no barrier between them.  SPLIT: one component
+// at a time through a float buffer (half the shared memory, three times the
+// barriers), else a float2 buffer.  s: the lane's slot (A-item).
+template <class IT, int P, bool SPLIT, bool REPEAT, int SA, int SQ>
+struct AsExchange {
+  using Elem = std::conditional_t<SPLIT, float, float2>;
+  static constexpr int N1 = IT::N1;
+  static constexpr int N2 = IT::N2;
+  static constexpr int IB = IT::IB;
+  static __device__ __forceinline__ bool has(int s, int ic) { return REPEAT || IT::item(s, ic); }
+  static __device__ __forceinline__ void to_items(Elem* buf, int s, int ab, const int (&bb)[IB], const float2 (&x)[N1],
+                                                  float2 (&y)[IB][N2]) {
+    if constexpr (SPLIT) {
+      static_for<0, 2>([&](auto c) {
+        static_for<0, N1>([&](auto k) { buf[ab + SA * k.value] = c.value ? x[k.value].y : x[k.value].x; });
+        exchange_sync<P>();
+        static_for<0, IB>([&](auto ic) {
+          if (!has(s, ic.value)) return;
+          static_for<0, N2>([&](auto q) {
+            const float v = buf[bb[ic.value] + SQ * q.value];
+            if constexpr (c.value) y[ic.value][q.value].y = v; else y[ic.value][q.value].x = v;
+          });
+        });
+        if constexpr (c.value == 0) exchange_sync<P>();
+      });
+    } else {
+      static_for<0, N1>([&](auto k) { buf[ab + SA * k.value] = x[k.value]; });
+      exchange_sync<P>();
+      static_for<0, IB>([&](auto ic) {
+        if (!has(s, ic.value)) return;
+        static_for<0, N2>([&](auto q) { y[ic.value][q.value] = buf[bb[ic.value] + SQ * q.value]; });
+      });
+    }
+    // lanes that repeat an item read entries another lane rewrites next
+    if constexpr (REPEAT && !IT::FULL_ROUNDS) exchange_sync<P>();
+  }
+  static __device__ __forceinline__ void to_vector(Elem* buf, int s, int ab, const int (&bb)[IB], const float2 (&y)[IB][N2],
+                                                   float2 (&x)[N1]) {
+    if constexpr (SPLIT) {
+      static_for<0, 2>([&](auto c) {
+        static_for<0, IB>([&](auto ic) {
+          if (!has(s, ic.value)) return;
+          static_for<0, N2>([&](auto q) {
+            buf[bb[ic.value] + SQ * q.value] = c.value ? y[ic.value][q.value].y : y[ic.value][q.value].x;
+          });
+        });
+        exchange_sync<P>();
+        static_for<0, N1>([&](auto k) {
+          const float v = buf[ab + SA * k.value];
+          if constexpr (c.value) x[k.value].y = v; else x[k.value].x = v;
+        });
+        if constexpr (c.value == 0) exchange_sync<P>();
+      });
+    } else {
+      static_for<0, IB>([&](auto ic) {
+        if (!has(s, ic.value)) return;
+        static_for<0, N2>([&](auto q) { buf[bb[ic.value] + SQ * q.value] = y[ic.value][q.value]; });
+      });
+      exchange_sync<P>();
+      static_for<0, N1>([&](auto k) { x[k.value] = buf[ab + SA * k.value]; });
+    }
+  }
+};
+
+// Long items (more than 16 values of a vector or of its items per lane): an
+// index goes through an empty asm statement, so that roots and addresses
+// derived from it are formed next to their use, not hoisted and kept live, and
+// scheduling barriers between the phases of a pass do the same for loads.
+// Short items have the registers, and their root and table loads are better
+// in flight early (64 points: column pass 14.7 -> 13.6 us); in the persistent
+// kinds (FENCED) they too would be kept live across the samples (256 points,
+// adjoint row pass 46 -> 60 us).
+template <class IT>
+__device__ __forceinline__ int opaque(int v) {
+  if constexpr (IT::LONG) asm volatile("" : "+v"(v));
+  return v;
+}
+template <class IT>
+__device__ __forceinline__ void phase() {
+  if constexpr (IT::LONG) __builtin_amdgcn_sched_barrier(0);
+}
+
+// Cooley-Tukey twiddles exp(-+2*pi*i*k1*j/N) of a B-item, eight at a time so
+// that their roots and products are not all live at once.  Items of 32 or
+// more: w^(k1*j) = w^(k1*(j mod 8)) * w^(8*k1*(j/8)), one more rounding
+// (<= 1.5 ulp) for 7 + N2/8 - 1 loads instead of N2 - 1.
+template <class IT, bool INV>
+__device__ __forceinline__ void as_twiddle(int k1, float2 (&y)[IT::N2]) {
+  constexpr int N2 = IT::N2;
+  auto root = [&](int m) { return root_at<IT::N>(INV ? (unsigned)(IT::N - k1 * m) : (unsigned)(k1 * m)); };
+  if constexpr (N2 >= 32) {
+    float2 lo[8];
+    static_for<1, 8>([&](auto i) { lo[i.value] = root(i.value); });
+    static_for<0, N2 / 8>([&](auto bc) {
+      constexpr int b = decltype(bc)::value;
+      if constexpr (b == 0) {
+        static_for<1, 8>([&](auto i) { y[i.value] = cmul(y[i.value], lo[i.value]); });
+      } else {
+        const float2 hi = root(8 * b);
+        y[8 * b] = cmul(y[8 * b], hi);
+        static_for<1, 8>([&](auto i) { y[8 * b + i.value] = cmul(y[8 * b + i.value], cmul(lo[i.value], hi)); });
+      }
+      phase<IT>();
+    });
+  } else {
+    static_for<1, N2>([&](auto j) {
+      y[j.value] = cmul(y[j.value], root(j.value));
+      if constexpr (j.value % 8 == 7) phase<IT>();
+    });
+  }
+}
+template <class IT>
+__device__ __forceinline__ void as_b_forward(int k1, float2 (&y)[IT::N2]) {
+  as_twiddle<IT, false>(opaque<IT>(k1), y);
+  phase<IT>();
+  Dft<IT::N2, -1>::run(y);
+  phase<IT>();
+}
+template <class IT>
+__device__ __forceinline__ void as_b_inverse(int k1, float2 (&y)[IT::N2]) {
+  Dft<IT::N2, 1>::run(y);
+  phase<IT>();
+  as_twiddle<IT, true>(opaque<IT>(k1), y);
+  phase<IT>();
+}
+
+// A-step of the elements u[0..KN) a lane holds (HALF: the middle half).
+template <class IT, bool HALF>
+__device__ __forceinline__ void as_a_forward(const float2 (&u)[IT::KN(HALF)], float2 (&x)[IT::N1]) {
+  if constexpr (HALF) {
+    HalfDft<IT::N1>::forward(u, x);
+  } else {
+    static_for<0, IT::N1>([&](auto k) { x[k.value] = u[k.value]; });
+    Dft<IT::N1, -1>::run(x);
+  }
+}
+template <class IT, bool HALF>
+__device__ __forceinline__ void as_a_inverse(float2 (&x)[IT::N1], float2 (&u)[IT::KN(HALF)]) {
+  if constexpr (HALF) {
+    HalfDft<IT::N1>::inverse(x, u);
+  } else {
+    Dft<IT::N1, 1>::run(x);
+    static_for<0, IT::N1>([&](auto k) { u[k.value] = x[k.value]; });
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Row passes.  A workgroup transforms R whole rows; lane (r, j), j < N2, holds
+// A-item j of row r, consecutive lanes consecutive elements, so every access
+// of a wave covers N2 consecutive values of R rows.  R*N2 is one wave where
+// N2 allows (no barriers at all; 60 of 64 lanes at N2 = 10 and 20, 56 at 14),
+// 8 rows in five waves at N2 = 40.
+// ---------------------------------------------------------------------------
+template <class PL>
+struct AsRows : AsItems<PL> {
+  using IT = AsItems<PL>;
+  static constexpr int R = IT::N2 <= 32 ? 64 / IT::N2 : 8;
+  static constexpr int P = (R * IT::N2 + 63) / 64 * 64;
+  // row pitch: at least the exchange area, and = N2 mod 64, so that the rows
+  // of a wave tile the banks on the A side
+  static constexpr int PR = IT::N1 * IT::P1 + (64 + IT::N2 - IT::N1 * IT::P1 % 64) % 64;
+  // one component at a time where the complex buffer would keep fewer than
+  // 16 waves resident per CU
+  static constexpr bool SPLIT = R * PR * 8 > 10 * 1024 * (P / 64);
+  // waves per SIMD asked of the compiler: 4 where a lane's items fit in 128
+  // registers, one less for the 40-value items and for the accumulating kinds
+  static constexpr int WAVES = IT::N2 * IT::IB > 32 ? 3 : 4;
+  static constexpr int WAVES_ACC = WAVES - 1;
+  static_assert(R * PR * (SPLIT ? 4 : 8) + R * kMaxRegions * 4 < 64 * 1024, "static shared memory");
+};
+
+template <class PL, int KIND, bool HALF>
+__global__ void __launch_bounds__(AsRows<PL>::P, (KIND == kAsRowBwdMid || KIND == kAsRowBwdLast)
+                                                     ? AsRows<PL>::WAVES_ACC : AsRows<PL>::WAVES)
+    as_row_pass(PassArgs a) {
+  using W = AsRows<PL>;
+  using IT = AsItems<PL, KIND == kAsRowBwdMid || KIND == kAsRowBwdLast>;
+  using EX = AsExchange<IT, W::P, W::SPLIT, true, W::P1, 1>;
+  constexpr int N = W::N;
+  constexpr int N1 = W::N1;
+  constexpr int N2 = W::N2;
+  constexpr int IB = W::IB;
+  constexpr int R = W::R;
+  constexpr int KN = W::KN(HALF);
+  constexpr bool ACC = (KIND == kAsRowBwdMid || KIND == kAsRowBwdLast);
+  constexpr bool SPECTRAL_IN = (KIND == kAsRowMid || KIND == kAsRowLast || KIND == kAsRowIfft || ACC);
+  constexpr bool FWD_OUT = (KIND == kAsRowFirst || KIND == kAsRowMid || KIND == kAsRowBwdFirst ||
+                            KIND == kAsRowBwdMid);
+  __shared__ typename EX::Elem buf[R * W::PR];
+  __shared__ float rsum[KIND == kAsRowLast ? R * kMaxRegions : 1];
+
+  const int rank = (int)blockIdx.x;
+  if (rank >= a.workers) return;
+  const int tid = (int)threadIdx.x;
+  // the lanes past the R rows repeat the first items of row 0 (the same values
+  // to the same shared-memory entries, no branch) and store nothing
+  const bool act = R * N2 == W::P || tid < R * N2;
+  const int r = act ? tid / N2 : 0;
+  const int j0 = act ? tid - r * N2 : tid - R * N2;
+  const int n = a.n;
+  const int off = a.off;
+  const size_t nn = (size_t)n * n;
+  const int total = a.ntiles * a.batch;
+  const int ab = r * W::PR + j0;
+  int bb[IB];
+  static_for<0, IB>([&](auto ic) { bb[ic.value] = r * W::PR + W::P1 * IT::template item_of<true>(j0, ic.value); });
+
+  float acc[ACC ? KN : 1];
+  if constexpr (ACC) {
+    static_for<0, KN>([&](auto k) { acc[k.value] = 0.f; });
+  }
+
+  auto item = [&](int it) {
+    const int tile = it % a.ntiles;
+    const int b = it / a.ntiles;
+    const int j = opaque<IT>(j0);
+    const int vec = tile * R + r;
+    const bool vok = vec < n;
+    auto pos_ok = [&](int jj, auto k) { return HALF || (unsigned)(jj + N2 * decltype(k)::value - off) < (unsigned)n; };
+    // f(k, byte offset per lane, scalar byte offset) for the elements of this
+    // lane's A-item in an n x n natural array of es-byte values; the per-lane
+    // offset is out of range outside the aperture
+    auto each_if = [&](bool ok, int es, auto&& f) {
+      const int jj = opaque<IT>(j);
+      const int row = vec * n + jj;  // HALF: element k is aperture position jj + N2*k
+      if constexpr (HALF) {
+        const unsigned base = ok ? (unsigned)(row * es) : kOutOfRange;
+        static_for<0, KN>([&](auto k) { f(k, base, N2 * k.value * es); });
+      } else {
+        static_for<0, KN>([&](auto k) {
+          f(k, ok && pos_ok(jj, k) ? (unsigned)((row + N2 * k.value - off) * es) : kOutOfRange, 0);
+        });
+      }
+    };
+    auto each = [&](int es, auto&& f) { each_if(vok, es, f); };
+    auto each_out = [&](int es, auto&& f) { each_if(vok && act, es, f); };
+    // spectrum element (round ic, k2) of this row: frequency k1 + N1*k2
+    auto spec_base = [&](bool ok, int ic) -> unsigned {
+      return ok ? (unsigned)(vec * N + IT::template item_of<true>(j, ic)) * 8u : kOutOfRange;
+    };
+    if constexpr (KIND == kAsRowLast) {
+      // sums only: rows no region covers contribute nothing
+      if (!a.intensity && !a.field_out && !a.saved_ud) {
+        if (!a.sums_part) return;
+        const bool hit = vok && a.row_mask[vec] != 0ull;
+        bool any;
+        if constexpr (W::P == 64) any = __any(hit) != 0; else any = __syncthreads_or(hit) != 0;
+        if (!any) {
+          for (int k = tid; k < a.K; k += W::P) a.sums_part[((size_t)b * a.ntiles + tile) * a.K + k] = 0.f;
+          return;
+        }
+      }
+    }
+
+    float2 u[KN];
+    if constexpr (SPECTRAL_IN) {
+      const Rsrc rin = make_rsrc(static_cast<const float2*>(a.in) + (size_t)b * n * N, (unsigned)(n * N) * 8u);
+      float2 y[IB][N2];
+      static_for<0, IB>([&](auto ic) {
+        const unsigned base = spec_base(vok, ic.value);
+        static_for<0, N2>([&](auto k2) { y[ic.value][k2.value] = bload_so<2>(rin, base, N1 * 8 * k2.value); });
+      });
+      const int ji = opaque<IT>(j);
+      static_for<0, IB>([&](auto ic) {
+        as_b_inverse<IT>(IT::template item_of<true>(ji, ic.value), y[ic.value]);
+      });
+      phase<IT>();
+      float2 x[N1];
+      EX::to_vector(buf, j, ab, bb, y, x);
+      phase<IT>();
+      as_a_inverse<IT, HALF>(x, u);
+      phase<IT>();
+      if constexpr (KIND == kAsRowMid || ACC) {
+        const Rsrc rmod = make_rsrc(a.mod, (unsigned)nn * 8u);
+        if constexpr (KIND == kAsRowMid) {
+          each(8, [&](auto k, unsigned o, int so) { u[k.value] = cmul(u[k.value], bload_keep_so(rmod, o, so)); });
+          if (a.act_out) {
+            const Rsrc ro = make_rsrc(a.act_out + (size_t)b * nn, (unsigned)nn * 8u);
+            each_out(8, [&](auto k, unsigned o, int so) { bstore_so(ro, o, so, u[k.value]); });
+          }
+        } else {
+          const Rsrc ra = make_rsrc(a.act_in + (size_t)b * nn, (unsigned)nn * 8u);
+          each(8, [&](auto k, unsigned o, int so) {
+            const float2 ul = bload_so<2>(ra, o, so);
+            acc[k.value] += ul.x * u[k.value].y - ul.y * u[k.value].x;
+          });
+          if constexpr (KIND == kAsRowBwdMid) {
+            phase<IT>();
+            each(8, [&](auto k, unsigned o, int so) { u[k.value] = cmulc(u[k.value], bload_keep_so(rmod, o, so)); });
+          }
+        }
+      }
+    } else if constexpr (KIND == kAsRowBwdFirst) {
+      // seed G_D = 2 (dL/dI) U_D; off the regions of a region loss U_D is not read
+      const Rsrc rud = make_rsrc(a.ud_in + (size_t)b * nn, (unsigned)nn * 8u);
+      if (a.grad_int) {
+        const Rsrc rg = make_rsrc(a.grad_int + (size_t)b * nn, (unsigned)nn * 4u);
+        each(8, [&](auto k, unsigned o, int so) { u[k.value] = bload_so<2>(rud, o, so); });
+        each(4, [&](auto k, unsigned o, int so) { u[k.value] = cscale(u[k.value], 2.f * bload_f_so(rg, o, so)); });
+      } else {
+        const float* __restrict__ gs = a.grad_sums + (size_t)b * a.K;
+        const unsigned long long vmask = vok ? a.row_mask[vec] : 0ull;
+        each(8, [&](auto k, unsigned o, int so) {
+          float g = 0.f;
+          if (vmask && pos_ok(j, k)) {
+            unsigned long long m = vmask & a.col_mask[j + N2 * (k.value + IT::K0(HALF)) - off];
+            while (m) {
+              g += gs[__builtin_ctzll(m)];
+              m &= m - 1;
+            }
+          }
+          // (zero, not 0 * U_D, where no region is)
+          const float2 v = bload_so<2>(rud, g != 0.f ? o : kOutOfRange, so);
+          u[k.value] = cscale(v, 2.f * g);
+        });
+      }
+    } else {  // kAsRowFirst: natural amplitudes or fields
+      if (a.in_real) {
+        const Rsrc ri = make_rsrc(static_cast<const float*>(a.in) + (size_t)b * nn, (unsigned)nn * 4u);
+        each(4, [&](auto k, unsigned o, int so) { u[k.value] = c2(bload_f_so(ri, o, so), 0.f); });
+      } else {
+        const Rsrc ri = make_rsrc(static_cast<const float2*>(a.in) + (size_t)b * nn, (unsigned)nn * 8u);
+        each(8, [&](auto k, unsigned o, int so) { u[k.value] = bload_so<2>(ri, o, so); });
+      }
+    }
+
+    if constexpr (FWD_OUT) {
+      phase<IT>();
+      float2 x[N1];
+      as_a_forward<IT, HALF>(u, x);
+      phase<IT>();
+      float2 y[IB][N2];
+      EX::to_items(buf, j, ab, bb, x, y);
+      phase<IT>();
+      const int jf = opaque<IT>(j);
+      const Rsrc ro = make_rsrc(a.out + (size_t)b * n * N, (unsigned)(n * N) * 8u);
+      // centred: position p holds frequency (p + N/2) mod N, a rotation of k2 by N2/2
+      const int rot = a.spec_centred ? N * 4 : 0;
+      static_for<0, IB>([&](auto ic) {
+        as_b_forward<IT>(IT::template item_of<true>(jf, ic.value), y[ic.value]);
+        const unsigned base = spec_base(vok && act && IT::item(jf, ic.value), ic.value);
+        static_for<0, N2>([&](auto k2) {
+          bstore_so(ro, base, N1 * 8 * k2.value + (k2.value < N2 / 2 ? rot : -rot), y[ic.value][k2.value]);
+        });
+      });
+    } else if constexpr (KIND == kAsRowIfft) {
+      const Rsrc ro = make_rsrc(a.out + (size_t)b * nn, (unsigned)nn * 8u);
+      each_out(8, [&](auto k, unsigned o, int so) { bstore_so(ro, o, so, u[k.value]); });
+    } else if constexpr (KIND == kAsRowLast) {
+      if (a.skip) {
+        const Rsrc rs = make_rsrc(a.skip + (size_t)b * nn, (unsigned)nn * 8u);
+        each(8, [&](auto k, unsigned o, int so) {
+          const float2 s = bload_so<2>(rs, o, so);
+          u[k.value] = cadd(u[k.value], s);
+        });
+      }
+      if (a.field_out) {
+        const Rsrc ro = make_rsrc(a.field_out + (size_t)b * nn, (unsigned)nn * 8u);
+        each_out(8, [&](auto k, unsigned o, int so) { bstore_so(ro, o, so, u[k.value]); });
+      }
+      if (a.saved_ud) {
+        const Rsrc ro = make_rsrc(a.saved_ud + (size_t)b * nn, (unsigned)nn * 8u);
+        each_out(8, [&](auto k, unsigned o, int so) { bstore_so(ro, o, so, u[k.value]); });
+      }
+      if (a.intensity) {
+        const Rsrc ro = make_rsrc(a.intensity + (size_t)b * nn, (unsigned)nn * 4u);
+        each_out(4, [&](auto k, unsigned o, int so) {
+          float v = cabs2(u[k.value]);
+          if (a.accumulate) v += bload_f_so(ro, o, so);
+          bstore_f_so(ro, o, so, v);
+        });
+      }
+      if (a.sums_part) {
+        // |U|^2 by aperture position (the row pitch holds n <= N values),
+        // then one run per (region, row) and the rows added in order
+        float* const pix = reinterpret_cast<float*>(buf);
+        exchange_sync<W::P>();
+        static_for<0, KN>([&](auto k) {
+          if (vok && pos_ok(j, k)) pix[r * W::PR + j + N2 * (k.value + IT::K0(HALF)) - off] = cabs2(u[k.value]);
+        });
+        exchange_sync<W::P>();
+        const int K = a.K;
+        const int side = a.det_size;
+        for (int i = tid; i < K * R; i += W::P) {
+          const int k = i / R;
+          const int rr = i - k * R;
+          const int2 c = a.regions[k];  // (y0, x0)
+          float run = 0.f;
+          if (tile * R + rr < n && (unsigned)(tile * R + rr - c.x) < (unsigned)side) {
+            for (int d = 0; d < side; ++d) run += pix[rr * W::PR + c.y + d];
+          }
+          rsum[i] = run;
+        }
+        exchange_sync<W::P>();
+        for (int k = tid; k < K; k += W::P) {
+          float part = 0.f;
+          for (int rr = 0; rr < R; ++rr) part += rsum[k * R + rr];
+          a.sums_part[((size_t)b * a.ntiles + tile) * K + k] = part;
+        }
+      }
+    }
+  };
+  // accumulating kinds run persistently, the others take one item
+  if constexpr (ACC) {
+    for (int it = rank; it < total; it += a.workers) item(it);
+  } else {
+    if (rank < total) item(rank);
+  }
+  if constexpr (ACC) {
+    // one partial per lane of workgroups (the tile is fixed): row-major, natural
+    const int j = j0;
+    const int vec = (rank % a.ntiles) * R + r;
+    const Rsrc dp = make_rsrc(a.dphi_part + (size_t)(rank / a.ntiles) * nn, (unsigned)nn * 4u);
+    static_for<0, KN>([&](auto k) {
+      const int q = j + N2 * (k.value + IT::K0(HALF)) - off;
+      bstore_f(dp, act && vec < n && (unsigned)q < (unsigned)n ? (unsigned)(vec * n + q) * 4u : kOutOfRange,
+               acc[k.value]);
+    });
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Column passes.  A workgroup transforms T spectrum columns of one sample;
+// consecutive lanes take consecutive columns.  The transfer function is read
+// from the caller's table H[ky][kx] in natural order; an even table
+// (H[N - ky] = H[ky]) is read at its rows ky <= N/2 only.  FAR: forward
+// transform only, x table, stored at [(ky + N/2) mod N][kx position].
+//
+// Work order, the ranks of an XCD contiguous: at the power-of-two lengths
+// pairs of neighbouring tiles sample by sample, pair after pair (an XCD reads
+// an eighth of the table, which stays in its L2: 156 against 161 us at 1024,
+// 64 samples of 512 rows; 31.5 against 33.9 at 512); at the others, whose
+// rows do not end on 128-byte lines, every tile of a sample, so that tiles
+// sharing a line run together (500 points, 32 samples: 54.2 against 60.8 us;
+// 400: 44.8 against 45.9; 200: 45.3 against 48.1).
+// ---------------------------------------------------------------------------
+template <class PL, int T>
+struct AsCols : AsItems<PL> {
+  using IT = AsItems<PL>;
+  static constexpr int P = T * IT::N2;
+  static_assert(P % 64 == 0, "whole waves");
+  static constexpr int LDS = IT::N1 * IT::P1 * T;
+  static constexpr bool PAIRS = (IT::N & (IT::N - 1)) == 0;
+  static constexpr bool SPLIT = LDS * 8 > 10 * 1024 * (P / 64);  // as for the rows
+  static constexpr int WAVES = IT::N2 * IT::IB > 32 ? 3 : 4;
+};
+
+template <class PL, int T, bool HALF, bool FAR>
+__global__ void __launch_bounds__((AsCols<PL, T>::P), (AsCols<PL, T>::WAVES)) as_col_pass(PassArgs a) {
+  using W = AsCols<PL, T>;
+  using IT = AsItems<PL>;
+  using EX = AsExchange<IT, W::P, W::SPLIT, false, W::P1 * T, T>;
+  constexpr int N = W::N;
+  constexpr int N1 = W::N1;
+  constexpr int N2 = W::N2;
+  constexpr int IB = W::IB;
+  constexpr int KN = W::KN(HALF);
+  __shared__ typename EX::Elem buf[W::LDS];
+
+  const int per = (int)gridDim.x >> 3;
+  const int item = ((int)blockIdx.x & 7) * per + ((int)blockIdx.x >> 3);
+  if (item >= a.workers) return;
+  int tile;
+  int b;
+  if constexpr (W::PAIRS) {
+    // (pair, sample, tile of the pair); a last odd tile is a pair of one
+    const int pair = item / (2 * a.batch);
+    const int rest = item - pair * 2 * a.batch;
+    const bool whole = 2 * pair + 1 < a.ntiles;
+    b = whole ? rest >> 1 : rest;
+    tile = 2 * pair + (whole ? rest & 1 : 0);
+  } else {
+    b = item / a.ntiles;
+    tile = item - b * a.ntiles;
+  }
+
+  const int tid = (int)threadIdx.x;
+  const int v = tid % T;
+  const int j = tid / T;
+  const int n = a.n;
+  const int off = a.off;
+  const int vec = tile * T + v;
+  const bool vok = vec < N;
+  const int ab = j * T + v;
+  int bb[IB];
+  static_for<0, IB>([&](auto ic) { bb[ic.value] = IT::template item_of<false>(j, ic.value) * W::P1 * T + v; });
+  // f(k, byte offset per lane, scalar byte offset) of this lane's A-item: rows
+  // pos - off of column vec
+  auto each = [&](auto&& f) {
+    const int jj = opaque<IT>(j);
+    if constexpr (HALF) {
+      const unsigned base = vok ? (unsigned)(jj * N + vec) * 8u : kOutOfRange;
+      static_for<0, KN>([&](auto k) { f(k, base, N2 * k.value * N * 8); });
+    } else {
+      static_for<0, KN>([&](auto k) {
+        const int q = jj + N2 * k.value - off;
+        f(k, vok && (unsigned)q < (unsigned)n ? (unsigned)(q * N + vec) * 8u : kOutOfRange, 0);
+      });
+    }
+  };
+
+  const Rsrc rin = make_rsrc(static_cast<const float2*>(a.in) + (size_t)b * n * N, (unsigned)(n * N) * 8u);
+  float2 u[KN];
+  each([&](auto k, unsigned o, int so) { u[k.value] = bload_so<2>(rin, o, so); });
+  float2 x[N1];
+  as_a_forward<IT, HALF>(u, x);
+  phase<IT>();
+  float2 y[IB][N2];
+  EX::to_items(buf, j, ab, bb, x, y);
+  phase<IT>();
+
+  // rows ky = k1 + N1*k2; the mirrored row N - ky = (N1 - k1) + N1*(N2 - 1 - k2)
+  const Rsrc rt = make_rsrc(a.tab, (unsigned)(N * N) * 8u);
+  const float sg = a.conj_tab ? -1.f : 1.f;  // (one product, not a branch per value)
+  const bool sym = a.tab_sym != 0;
+  int kx = vec;
+  if constexpr (FAR) kx = vec + N / 2 < N ? vec + N / 2 : vec - N / 2;  // centred columns
+  static_for<0, IB>([&](auto ic) {
+    if (!IT::item(j, ic.value)) return;
+    const int k1 = j + N2 * ic.value;
+    float2(&z)[N2] = y[ic.value];
+    as_b_forward<IT>(k1, z);
+    const unsigned lo = vok ? (unsigned)(k1 * N + kx) * 8u : kOutOfRange;
+    const unsigned hi = vok && sym ? (unsigned)((N1 - k1) * N + kx) * 8u : lo;
+    static_for<0, N2>([&](auto k2) {
+      constexpr int up = N1 * N * 8 * decltype(k2)::value;
+      constexpr int down = N1 * N * 8 * (N2 - 1 - decltype(k2)::value);
+      const float2 h = k2.value < N2 / 2 ? bload_keep_so(rt, lo, up) : bload_keep_so(rt, hi, sym ? down : up);
+      z[k2.value] = cmul(z[k2.value], c2(h.x, sg * h.y));
+      if constexpr (k2.value % 8 == 7) phase<IT>();  // eight table values in flight
+    });
+    if constexpr (FAR) {
+      const Rsrc ro = make_rsrc(a.out + (size_t)b * N * N, (unsigned)(N * N) * 8u);
+      const unsigned out = vok ? (unsigned)(k1 * N + vec) * 8u : kOutOfRange;
+      static_for<0, N2>([&](auto k2) {
+        constexpr int row = N1 * ((decltype(k2)::value + N2 / 2) % N2);  // (ky + N/2) mod N = k1 + row
+        bstore_so(ro, out, row * N * 8, z[k2.value]);
+      });
+    } else {
+      phase<IT>();
+      as_b_inverse<IT>(k1, z);
+    }
+  });
+  if constexpr (!FAR) {
+    EX::to_vector(buf, j, ab, bb, y, x);
+    phase<IT>();
+    as_a_inverse<IT, HALF>(x, u);
+    const Rsrc ro = make_rsrc(a.out + (size_t)b * n * N, (unsigned)(n * N) * 8u);
+    each([&](auto k, unsigned o, int so) { bstore_so(ro, o, so, cscale(u[k.value], a.scale)); });
+  }
+}
+
+// Columns per workgroup: whole waves of T * N2 threads, and 128-byte segments
+// of every row (at 1024 points 8 columns, four waves instead of eight per
+// workgroup, measured 181 against 156 us for 64 samples of 512 rows, at 1000
+// 54.8 against 44.5 us for 8 of 1000; 32 columns at 256 and 512 5% slower).
+template <int N> struct AsColT { static constexpr int T = 16; };
+template <> struct AsColT<100>  { static constexpr int T = 32; };
+template <> struct AsColT<200>  { static constexpr int T = 32; };
+template <> struct AsColT<350>  { static constexpr int T = 32; };
+
+// n = N/2 centred and N1 divisible by 4: HalfDft.
+template <int N>
+constexpr bool as_half_plan() { return AsPlanFor<N>::type::N1 % 4 == 0; }
+template <int N>
+bool as_half(const PassArgs& a) { return as_half_plan<N>() && 2 * a.n == N && 4 * a.off == N; }
+
+template <int N, int KIND, bool HALF>
+hipError_t launch_as_row(const PassArgs& a, hipStream_t st) {
+  using PL = typename AsPlanFor<N>::type;
+  hipLaunchKernelGGL((as_row_pass<PL, KIND, HALF>), dim3(a.workers), dim3(AsRows<PL>::P), 0, st, a);
+  return hipGetLastError();
+}
+template <int N, int KIND>
+hipError_t launch_as_row(const PassArgs& a, hipStream_t st) {
+  if (a.workers < 1 || a.n < 1 || a.n > N || a.off != (N - a.n) / 2) return hipErrorInvalidValue;
+  if constexpr (as_half_plan<N>()) {
+    if (as_half<N>(a)) return launch_as_row<N, KIND, true>(a, st);
+  }
+  return launch_as_row<N, KIND, false>(a, st);
+}
+
+template <int N, bool FAR>
+hipError_t launch_as_col(const PassArgs& args, hipStream_t st) {
+  using PL = typename AsPlanFor<N>::type;
+  constexpr int T = AsColT<N>::T;
+  PassArgs a = args;
+  if (a.batch < 1 || a.n < 1 || a.n > N || a.off != (N - a.n) / 2) return hipErrorInvalidValue;
+  a.ntiles = (N + T - 1) / T;
+  a.workers = a.ntiles * a.batch;
+  const dim3 grid(8 * ((a.workers + 7) / 8));
+  if constexpr (as_half_plan<N>()) {
+    if (as_half<N>(a)) {
+      hipLaunchKernelGGL((as_col_pass<PL, T, true, FAR>), grid, dim3(T * PL::N2), 0, st, a);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((as_col_pass<PL, T, false, FAR>), grid, dim3(T * PL::N2), 0, st, a);
+  return hipGetLastError();
+}
+
+template <int N>
+hipError_t launch_as_n(AsPassKind kind, const PassArgs& a, hipStream_t st) {
+  switch (kind) {
+    case kAsRowFirst: return launch_as_row<N, kAsRowFirst>(a, st);
+    case kAsCol: return launch_as_col<N, false>(a, st);
+    case kAsRowMid: return launch_as_row<N, kAsRowMid>(a, st);
+    case kAsRowLast: return launch_as_row<N, kAsRowLast>(a, st);
+    case kAsRowBwdFirst: return launch_as_row<N, kAsRowBwdFirst>(a, st);
+    case kAsRowBwdMid: return launch_as_row<N, kAsRowBwdMid>(a, st);
+    case kAsRowBwdLast: return launch_as_row<N, kAsRowBwdLast>(a, st);
+    case kAsRowIfft: return launch_as_row<N, kAsRowIfft>(a, st);
+    case kAsColFar: return launch_as_col<N, true>(a, st);
+  }
+  return hipErrorInvalidValue;
+}
+
+// Rows per workgroup, and resident workgroups of an accumulating row kind.
+template <int N>
+int as_rows_n() { return AsRows<typename AsPlanFor<N>::type>::R; }
+template <int N>
+int slots_as_n(AsPassKind kind, bool half) {
+  using PL = typename AsPlanFor<N>::type;
+  static int cache[2][2] = {};
+  const int m = kind == kAsRowBwdMid ? 0 : 1;
+  int& c = cache[m][half ? 1 : 0];
+  if (c == 0) {
+    const void* k = m == 0 ? reinterpret_cast<const void*>(&as_row_pass<PL, kAsRowBwdMid, false>)
+                           : reinterpret_cast<const void*>(&as_row_pass<PL, kAsRowBwdLast, false>);
+    if constexpr (as_half_plan<N>()) {
+      if (half)
+        k = m == 0 ? reinterpret_cast<const void*>(&as_row_pass<PL, kAsRowBwdMid, true>)
+                   : reinterpret_cast<const void*>(&as_row_pass<PL, kAsRowBwdLast, true>);
+    }
+    c = resident_per_cu(k, AsRows<PL>::P);
+  }
+  return c * device_cus();
+}
+
+}  // namespace lr

@@ -278,4 +278,56 @@ template <int SIGN> struct Dft<32, SIGN> : DftCT<4, 8, SIGN> {};
 template <int SIGN> struct Dft<40, SIGN> : DftPFA<8, 5, SIGN> {};
 template <int SIGN> struct Dft<14, SIGN> : DftPFA<2, 7, SIGN> {};
 
+// Length-R transforms whose spatial side is the middle half of the range,
+// x[n] with n = R/4 .. 3R/4 - 1 (a field zero padded to twice its size):
+// element n is held as x[n - R/4].  One radix-2 stage of the full transform
+// has a single non-zero term per output and disappears:
+//   forward: X[2k] = DFT_{R/2}(x[n] at n mod R/2)[k], X[2k+1] the same of
+//            x[n] w^n, w = exp(-2*pi*i/R);
+//   inverse (to the middle half): x[n] = IDFT_{R/2}(X[2k])[n mod R/2]
+//            + w^-n IDFT_{R/2}(X[2k+1])[n mod R/2].
+template <int R>
+struct HalfDft {
+  static_assert(R % 4 == 0, "the middle half starts at R/4");
+  static constexpr int H = R / 2;
+  static constexpr int Q = R / 4;
+  LR_HD static void forward(const float2* x, float2* X) {
+    float2 e[H];
+    float2 o[H];
+    static_for<0, H>([&](auto i) {
+      constexpr int n = decltype(i)::value + Q;
+      e[n % H] = x[n - Q];
+      o[n % H] = twiddle_const<R, -1, n>(x[n - Q]);
+    });
+    Dft<H, -1>::run(e);
+    Dft<H, -1>::run(o);
+    static_for<0, H>([&](auto k) {
+      X[2 * k.value] = e[k.value];
+      X[2 * k.value + 1] = o[k.value];
+    });
+  }
+  LR_HD static void inverse(const float2* X, float2* x) {
+    float2 e[H];
+    float2 o[H];
+    static_for<0, H>([&](auto k) {
+      e[k.value] = X[2 * k.value];
+      o[k.value] = X[2 * k.value + 1];
+    });
+    Dft<H, 1>::run(e);
+    Dft<H, 1>::run(o);
+    static_for<0, H>([&](auto i) {
+      constexpr int n = decltype(i)::value + Q;
+      if constexpr ((4 * n) % R == 0) {
+        x[n - Q] = cadd(e[n % H], twiddle_const<R, 1, n>(o[n % H]));
+      } else {
+        constexpr cdbl z = unit_root(n, R, 1);
+        constexpr float wr = static_cast<float>(z.re);
+        constexpr float wi = static_cast<float>(z.im);
+        const float2 u = o[n % H];
+        x[n - Q] = c2(fmaf(wr, u.x, fmaf(-wi, u.y, e[n % H].x)), fmaf(wr, u.y, fmaf(wi, u.x, e[n % H].y)));
+      }
+    });
+  }
+};
+
 }  // namespace lr

@@ -11,7 +11,8 @@ template <int N> hipError_t launch_fr_n(PassKind, Axis, const PassArgs&, hipStre
 template <int N> int slots_fr_n(PassKind, Axis, bool);
 template <int N> int tile_fr_n(PassKind, Axis, bool);
 template <int N> hipError_t launch_as_n(AsPassKind, const PassArgs&, hipStream_t);
-template <int N> hipError_t prep_as_n(const float2*, float2*, float, int, hipStream_t);
+template <int N> int as_rows_n();
+template <int N> int slots_as_n(AsPassKind, bool);
 template <int N> TileShape shape_n();
 template <int N> SlotMap slot_map_n();
 template <int N> hipError_t launch_field_fwd_n(const FieldArgs&, hipStream_t);
@@ -43,15 +44,20 @@ __device__ __forceinline__ void prep_mod_body(const float* __restrict__ phi, int
   }
 }
 
-__global__ void finish_sums_kernel(const float* __restrict__ part, int batch, int ntiles, int K, float* __restrict__ sums,
-                                   int accumulate) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+// sums[b][k] (one wave each): the per-tile partial sums, lane l adding tiles
+// l, l + 64, ... and the lanes a fixed butterfly.  One thread per sum walked
+// up to 256 tiles one load at a time (20 us for 1000 sums of 67 tiles).
+__global__ void __launch_bounds__(256) finish_sums_kernel(const float* __restrict__ part, int batch, int ntiles, int K,
+                                                          float* __restrict__ sums, int accumulate) {
+  const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (i >= batch * K) return;
+  const int lane = threadIdx.x & 63;
   const int b = i / K;
   const int k = i - b * K;
   float s = 0.f;
-  for (int tl = 0; tl < ntiles; ++tl) s += part[((size_t)b * ntiles + tl) * K + k];
-  sums[i] = accumulate ? sums[i] + s : s;
+  for (int tl = lane; tl < ntiles; tl += 64) s += part[((size_t)b * ntiles + tl) * K + k];
+  s = wave_sum(s);
+  if (lane == 0) sums[i] = accumulate ? sums[i] + s : s;
 }
 
 // Loss of the detector sums, averaged over the batch, and its gradient
@@ -553,20 +559,37 @@ hipError_t launch_as_pass(int N, AsPassKind kind, const PassArgs& a, hipStream_t
 }
 
 
-hipError_t launch_prep_as_table(int N, const float2* H, float2* Hp, float scale, int centred, hipStream_t st) {
+int as_row_tile(int N) {
   switch (N) {
-    case 64: return prep_as_n<64>(H, Hp, scale, centred, st);
-    case 100: return prep_as_n<100>(H, Hp, scale, centred, st);
-    case 128: return prep_as_n<128>(H, Hp, scale, centred, st);
-    case 200: return prep_as_n<200>(H, Hp, scale, centred, st);
-    case 256: return prep_as_n<256>(H, Hp, scale, centred, st);
-    case 350: return prep_as_n<350>(H, Hp, scale, centred, st);
-    case 400: return prep_as_n<400>(H, Hp, scale, centred, st);
-    case 500: return prep_as_n<500>(H, Hp, scale, centred, st);
-    case 512: return prep_as_n<512>(H, Hp, scale, centred, st);
-    case 1000: return prep_as_n<1000>(H, Hp, scale, centred, st);
-    case 1024: return prep_as_n<1024>(H, Hp, scale, centred, st);
-    default: return hipErrorInvalidValue;
+    case 64: return as_rows_n<64>();
+    case 100: return as_rows_n<100>();
+    case 128: return as_rows_n<128>();
+    case 200: return as_rows_n<200>();
+    case 256: return as_rows_n<256>();
+    case 350: return as_rows_n<350>();
+    case 400: return as_rows_n<400>();
+    case 500: return as_rows_n<500>();
+    case 512: return as_rows_n<512>();
+    case 1000: return as_rows_n<1000>();
+    case 1024: return as_rows_n<1024>();
+    default: return 0;
+  }
+}
+
+int as_pass_slots(int N, AsPassKind kind, bool half) {
+  switch (N) {
+    case 64: return slots_as_n<64>(kind, half);
+    case 100: return slots_as_n<100>(kind, half);
+    case 128: return slots_as_n<128>(kind, half);
+    case 200: return slots_as_n<200>(kind, half);
+    case 256: return slots_as_n<256>(kind, half);
+    case 350: return slots_as_n<350>(kind, half);
+    case 400: return slots_as_n<400>(kind, half);
+    case 500: return slots_as_n<500>(kind, half);
+    case 512: return slots_as_n<512>(kind, half);
+    case 1000: return slots_as_n<1000>(kind, half);
+    case 1024: return slots_as_n<1024>(kind, half);
+    default: return 0;
   }
 }
 
@@ -718,7 +741,7 @@ hipError_t launch_prep_layers(const float* phi, int layers, int n, float gamma, 
 hipError_t launch_finish_sums(const float* part, int batch, int ntiles, int K, float* sums, int accumulate,
                               hipStream_t st) {
   const int total = batch * K;
-  hipLaunchKernelGGL(finish_sums_kernel, dim3((total + 255) / 256), dim3(256), 0, st, part, batch, ntiles, K, sums,
+  hipLaunchKernelGGL(finish_sums_kernel, dim3((total + 3) / 4), dim3(256), 0, st, part, batch, ntiles, K, sums,
                      accumulate);
   return hipGetLastError();
 }

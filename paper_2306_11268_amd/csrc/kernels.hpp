@@ -21,8 +21,8 @@ enum PassKind : int {
 };
 
 // Passes of the non-separable (angular-spectrum) path.  Fields between
-// passes hold rows of x-spectra: [B][n rows][N columns], columns in the
-// plan's location order.
+// passes hold rows of x-spectra: [B][n rows][N columns], columns in natural
+// frequency order.
 enum AsPassKind : int {
   kAsRowFirst = 0,   // rows: pad -> FFT_x (input amplitude or field)
   kAsCol = 1,        // columns: pad -> FFT_y -> x H -> IFFT_y -> crop
@@ -55,15 +55,16 @@ struct PassArgs {
   const void* in;
   int in_real;    // input is a real float amplitude
   float2* out;
-  // spectral table: B-item-ordered 1-D chirp (separable path) or the
-  // column-permuted 2-D transfer function (angular-spectrum path)
+  // spectral table: B-item-ordered 1-D chirp (separable path) or the 2-D
+  // transfer function H[ky][kx] (angular-spectrum path)
   const float2* tab;
   int conj_tab;
-  // modulation gamma*exp(j*phi_l), oriented [q][vec]
+  float scale;    // angular-spectrum column pass: factor of its output (1/N^2)
+  // modulation gamma*exp(j*phi_l), oriented [q][vec] (separable path) or natural [y][x]
   const float2* mod;
   int conj_mod;
-  float2* act_out;      // angular-spectrum path: U_l, oriented [B][n][n]
-  const float2* act_in; // angular-spectrum path: U_l, oriented; separable path: W_{l-1}, natural [B][n][n]
+  float2* act_out;      // angular-spectrum path: U_l, natural [B][n][n]
+  const float2* act_in; // angular-spectrum path: U_l; separable path: W_{l-1}; natural [B][n][n]
   // Adjoint column passes: when not NULL, the input field (G) is zero on the
   // rows y with live[y] == 0 (rows that no detector region covers, which the
   // detector-plane seed pass does not write); those rows are not read.
@@ -79,8 +80,8 @@ struct PassArgs {
   // reads and writes whole output columns
   int spec_centred;
   // angular-spectrum column pass: the table is even in ky (H[N - ky] =
-  // H[ky], exact for the analytic angular-spectrum transfer function), so
-  // only its rows ky <= N/2 are read
+  // H[ky], exact for the analytic angular-spectrum transfer function and the
+  // far-field table), so only its rows ky <= N/2 are read
   int tab_sym;
   // field added to the detector-plane field before any output or seed is
   // formed (natural [B][n][n]; nullable): an optical skip connection
@@ -179,11 +180,15 @@ hipError_t launch_fresnel_pass(int N, PassKind kind, Axis axis, const PassArgs& 
 // once, and the vectors each of its workgroups transforms.
 int fresnel_pass_slots(int N, PassKind kind, Axis axis, bool full);
 int fresnel_pass_tile(int N, PassKind kind, Axis axis, bool full);
+// Angular-spectrum passes: row kinds run PassArgs::workers workgroups over
+// PassArgs::ntiles tiles of as_row_tile(N) rows; column kinds set both
+// themselves.  as_pass_slots: workgroups of an accumulating row kind that fit
+// on the device at once (half: the aperture is the middle half of the grid).
 hipError_t launch_as_pass(int N, AsPassKind kind, const PassArgs& a, hipStream_t st);
+int as_row_tile(int N);
+int as_pass_slots(int N, AsPassKind kind, bool half);
 
 // Small helper kernels.
-// Hp[ky][c] = scale * H[ky][kx(c)] (columns in the row plan's slot order).
-hipError_t launch_prep_as_table(int N, const float2* H, float2* Hp, float scale, int centred, hipStream_t st);
 // sums[b][k] = (accumulate ? sums[b][k] : 0) + the per-tile partial sums, in tile order.
 hipError_t launch_finish_sums(const float* part, int batch, int ntiles, int K, float* sums, int accumulate,
                               hipStream_t st);

@@ -7,8 +7,7 @@
 // one along y; consecutive 1-D propagations along the same axis, with the
 // pointwise phase modulation of Eq. (phase_mod_matrix) between them, run in a
 // single pass over the field.  The angular-spectrum transfer function does not
-// factor; its hops use a row pass (FFT_x), a column pass (FFT_y, x H, IFFT_y)
-// and a row pass (IFFT_x, modulation, next FFT_x).
+// factor; its passes are in as_impl.hpp.
 //
 // Every thread owns one A-item (j = its slot) of its vector, so the A-step
 // data of a thread is a plain register array x[N1].  Global I/O of a tile is
@@ -36,18 +35,6 @@ __device__ __forceinline__ T ld(const T* base, unsigned idx) {
 template <class T>
 __device__ __forceinline__ void st(T* base, unsigned idx, T v) {
   *reinterpret_cast<T*>(reinterpret_cast<char*>(base) + idx * (unsigned)sizeof(T)) = v;
-}
-
-// Streaming variants for data touched once per pass (saved activations):
-// non-temporal hints keep them from displacing reused lines in the caches.
-__device__ __forceinline__ float2 ld_stream(const float2* base, unsigned idx) {
-  const unsigned long long u = __builtin_nontemporal_load(
-      reinterpret_cast<const unsigned long long*>(reinterpret_cast<const char*>(base) + idx * 8u));
-  return __builtin_bit_cast(float2, u);
-}
-__device__ __forceinline__ void st_stream(float2* base, unsigned idx, float2 v) {
-  __builtin_nontemporal_store(__builtin_bit_cast(unsigned long long, v),
-                              reinterpret_cast<unsigned long long*>(reinterpret_cast<char*>(base) + idx * 8u));
 }
 
 // Raw buffer access.  A buffer resource bounds every access to [0, bytes):
@@ -98,6 +85,9 @@ __device__ __forceinline__ float2 bload_so(Rsrc r, unsigned off, int soff) {
 }
 __device__ __forceinline__ float2 bload_keep_so(Rsrc r, unsigned off, int soff) {
   return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, soff, 0));
+}
+__device__ __forceinline__ float bload_f_so(Rsrc r, unsigned off, int soff) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, soff, 0));
 }
 __device__ __forceinline__ void bstore_so(Rsrc r, unsigned off, int soff, float2 v) {
   __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(lr_v2i, v), r, (int)off, soff, 0);
@@ -362,45 +352,6 @@ struct Mapped {
   __device__ __forceinline__ int operator()(int v) const { return map[v]; }
 };
 
-// Adjoint seed at the detector plane: G_D = 2 * (dL/dI) * U_D, with dL/dI a
-// full map or constant over each detector region (from dL/dS).
-template <class C, int AXIS>
-__device__ __forceinline__ void load_seed(float2* lds, const PassArgs& a, int b, int vec0, int nvalid) {
-  const int n = a.n;
-  const int off = a.off;
-  const size_t nn = (size_t)n * n;
-  zero_padding<C>(lds, n, off);
-  const float2* __restrict__ ud = a.ud_in + (size_t)b * nn;
-  const float* __restrict__ gint = a.grad_int ? a.grad_int + (size_t)b * nn : nullptr;
-  const float* __restrict__ gsum = a.grad_sums ? a.grad_sums + (size_t)b * a.K : nullptr;
-  constexpr int BUF = WalkShape<C, AXIS, kAll>::BUF;
-  float2 buf[BUF];
-  float g[BUF];
-  tile_walk2<C, AXIS, kAll, false>(n, off, nvalid,
-      [&](auto i, int v, int q, int, bool ok) {
-        float gv = 0.f;
-        float2 u = c2(0.f, 0.f);
-        if (ok) {
-          const int y = AXIS == kRow ? vec0 + v : q;
-          const int x = AXIS == kRow ? q : vec0 + v;
-          if (gint) {
-            gv = ld(gint, y * n + x);
-          } else {
-            // dL/dI is dL/dS_k on region k: sum over the regions covering (y, x)
-            unsigned long long mask = ld(a.row_mask, y) & ld(a.col_mask, x);
-            while (mask) {
-              gv += gsum[__builtin_ctzll(mask)];
-              mask &= mask - 1;
-            }
-          }
-          if (gv != 0.f) u = ld(ud, y * n + x);
-        }
-        g[i.value] = gv;
-        buf[i.value] = u;
-      },
-      [&](auto i, int, int, int li, bool) { lds[li] = cscale(buf[i.value], 2.f * g[i.value]); });
-}
-
 // Store a tile from shared memory into natural-layout rows/columns of an
 // n x n field (out, wave-uniform).
 template <class C, int AXIS, bool ST, class VF>
@@ -435,9 +386,8 @@ __device__ __forceinline__ void tile_outputs(const float2* lds, float* rsum, con
   const int off = a.off;
   const size_t nn = (size_t)n * n;
   float2* fo = a.field_out ? a.field_out + (size_t)b * nn : nullptr;
-  float2* sv = a.saved_ud ? a.saved_ud + (size_t)b * nn : nullptr;
   float* io = a.intensity ? a.intensity + (size_t)b * nn : nullptr;
-  if (fo || sv || io) {
+  if (fo || io) {
     float2 buf[WalkShape<C, AXIS, kStoreChunk>::BUF];
     tile_walk2<C, AXIS, kStoreChunk, false>(n, off, nvalid,
         [&](auto i, int, int, int li, bool) { buf[i.value] = lds[li]; },
@@ -445,7 +395,6 @@ __device__ __forceinline__ void tile_outputs(const float2* lds, float* rsum, con
           if (ok) {
             const int idx = nat_index<AXIS>(n, vf(v), q);
             if (fo) st(fo, idx, buf[i.value]);
-            if (sv) st(sv, idx, buf[i.value]);
             if (io) st(io, idx, a.accumulate ? ld(io, idx) + cabs2(buf[i.value]) : cabs2(buf[i.value]));
           }
         });
@@ -1022,252 +971,6 @@ __global__ void __launch_bounds__(C::P, C::WAVES) detector_pass(PassArgs a) {
         store_tile<C, AXIS, FULL>(lds, a.out + (size_t)b * nn, n, off, vfs, nvalid);
       }
     }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Angular-spectrum passes.  Between passes a sample is stored as n rows of
-// N x-spectrum values in the plan's slot order ([B][n][N]).
-// ---------------------------------------------------------------------------
-// (The B-item index goes behind an empty asm statement, as in b_spectral:
-// twiddle offsets derived from it are formed at their use, not hoisted out
-// of the per-sample loop.)
-template <class C>
-__device__ __forceinline__ void b_forward_all(const Tile<C>& t) {
-  int s = t.s;
-  asm volatile("" : "+v"(s));
-#pragma unroll 1
-  for (int ii = 0; ii < C::IB; ++ii) {
-    const int k1 = s + C::S * ii;
-    if (!C::B_FULL && k1 >= C::N1) break;
-    float2 y[C::N2];
-    read_b(t, k1, y);
-    b_forward<C>(k1, y);
-    write_b(t, k1, y);
-  }
-}
-template <class C>
-__device__ __forceinline__ void b_inverse_all(const Tile<C>& t) {
-  int s = t.s;
-  asm volatile("" : "+v"(s));
-#pragma unroll 1
-  for (int ii = 0; ii < C::IB; ++ii) {
-    const int k1 = s + C::S * ii;
-    if (!C::B_FULL && k1 >= C::N1) break;
-    float2 y[C::N2];
-    read_b(t, k1, y);
-    b_inverse<C>(k1, y);
-    write_b(t, k1, y);
-  }
-}
-
-// Spectrum rows (pitch N, slot order) of a row tile <-> shared memory (the
-// loads are non-temporal: each row is read once per pass).
-template <class C>
-__device__ __forceinline__ void load_spec_rows(float2* lds, const float2* __restrict__ in, int vec0, int nvalid) {
-  float2 buf[C::N1];
-  const int total = nvalid * C::N;
-  const int tid = opaque_tid();
-  static_for<0, C::N1>([&](auto i) {
-    const int e = tid + i.value * C::P;
-    if (e < total) buf[i.value] = ld_stream(in, vec0 * C::N + e);
-  });
-  static_for<0, C::N1>([&](auto i) {
-    const int e = tid + i.value * C::P;
-    const int v = e / C::N;
-    if (e < total) lds[(e - v * C::N) * C::TP + v] = buf[i.value];
-  });
-}
-// With centred, position p of a stored row holds frequency (p + N/2) mod N
-// instead of slot p (N even).
-template <class C>
-__device__ __forceinline__ void store_spec_rows(const float2* lds, float2* __restrict__ out, int vec0, int nvalid,
-                                                bool centred) {
-  using PL = typename C::Plan;
-  float2 buf[C::N1];
-  const int total = nvalid * C::N;
-  const int tid = opaque_tid();
-  static_for<0, C::N1>([&](auto i) {
-    const int e = tid + i.value * C::P;
-    const int v = e / C::N;
-    const int p = e - v * C::N;
-    const int slot = centred ? PL::slot_of_freq(p + C::N / 2 < C::N ? p + C::N / 2 : p - C::N / 2) : p;
-    if (e < total) buf[i.value] = lds[slot * C::TP + v];
-  });
-  static_for<0, C::N1>([&](auto i) {
-    const int e = tid + i.value * C::P;
-    if (e < total) st(out, vec0 * C::N + e, buf[i.value]);
-  });
-}
-
-template <class C, int KIND>
-__global__ void __launch_bounds__(C::P, (KIND == kAsRowBwdMid || KIND == kAsRowBwdLast || KIND == kAsRowMid)
-                                            ? C::WAVES_ACC : C::WAVES)
-    as_pass(PassArgs a) {
-  __shared__ float2 lds[C::LDS_ELEMS];
-  // region partial sums of the detector-plane outputs (row kinds that end in positions)
-  __shared__ float rsum[(KIND == kAsRowLast || KIND == kAsRowBwdLast || KIND == kAsRowIfft)
-                            ? C::T * kMaxRegions : 1];
-  using PL = typename C::Plan;
-  constexpr int N = C::N;
-  constexpr int N1 = C::N1;
-  constexpr bool ACC = (KIND == kAsRowBwdMid || KIND == kAsRowBwdLast);
-  constexpr bool LAYER = (KIND == kAsRowMid || ACC);
-  constexpr bool SPECTRAL_IN = (KIND == kAsRowMid || KIND == kAsRowLast || KIND == kAsRowBwdMid ||
-                                KIND == kAsRowBwdLast || KIND == kAsRowIfft);
-  constexpr bool FWD_OUT = (KIND == kAsRowFirst || KIND == kAsRowMid || KIND == kAsRowBwdFirst ||
-                            KIND == kAsRowBwdMid);
-  const Tile<C> t{lds, (int)(threadIdx.x % C::T), (int)(threadIdx.x / C::T)};
-  const int j = t.s;
-
-  const WorkItem wi = work_item(a.ntiles, (a.batch + a.spg - 1) / a.spg);
-  if (!wi.valid) return;
-  const int n = a.n;
-  const int off = a.off;
-  const size_t nn = (size_t)n * n;
-  const int vec0 = wi.tile * C::T;
-  const int vec = vec0 + t.v;
-  const int nvalid = min(C::T, a.nvec - vec0);
-  const bool vok = t.v < nvalid;
-  const int b0 = wi.group * a.spg;
-  const int b1 = min(a.batch, b0 + a.spg);
-
-  float acc[ACC ? N1 : 1];
-  if constexpr (ACC) {
-    static_for<0, N1>([&](auto k) { acc[k.value] = 0.f; });
-  }
-
-  for (int b = b0; b < b1; ++b) {
-    float2 x[N1];
-    if constexpr (KIND == kAsCol) {
-      // vectors: spectrum columns (slot order); positions: rows of the padded grid
-      const float2* __restrict__ in = static_cast<const float2*>(a.in) + (size_t)b * n * N;
-      __syncthreads();
-      load_a_direct<C>(in, N, n, off, vec, vok, x);
-      Dft<N1, -1>::run(x);
-      write_a(t, j, x);
-      __syncthreads();
-      // B-step with the 2-D table: element k2 of item k1 is ky = freq(k1, k2);
-      // scheduling barriers keep the twiddle and table loads next to their use.
-      // An even table is read at min(ky, N - ky): half the rows, so half the
-      // table traffic of a launch (each sample reads the whole table)
-      const bool cj = a.conj_tab != 0;
-      int s_op = t.s;
-      asm volatile("" : "+v"(s_op));
-#pragma unroll 1
-      for (int ii = 0; ii < C::IB; ++ii) {
-        const int k1 = s_op + C::S * ii;
-        if (!C::B_FULL && k1 >= C::N1) break;
-        float2 y[C::N2];
-        read_b(t, k1, y);
-        b_forward<C>(k1, y);
-        __builtin_amdgcn_sched_barrier(0);
-        if (vok) {
-          static_for<0, C::N2>([&](auto kc) {
-            constexpr int k2 = decltype(kc)::value;
-            const int ky = PL::freq(k1, k2);
-            const float2 h = ld(a.tab, (a.tab_sym && ky > N / 2 ? N - ky : ky) * N + vec);
-            y[k2] = cj ? cmulc(y[k2], h) : cmul(y[k2], h);
-          });
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        b_inverse<C>(k1, y);
-        __builtin_amdgcn_sched_barrier(0);
-        write_b(t, k1, y);
-      }
-      __syncthreads();
-      read_a(t, j, x);
-      Dft<N1, 1>::run(x);
-      store_a_direct<C>(a.out + (size_t)b * n * N, N, n, off, vec, vok, x);
-      continue;
-    }
-    if constexpr (KIND == kAsColFar) {
-      // unnormalised DFT along y of x-spectrum column vec, stored by the row
-      // pass in centred order (column vec holds kx = (vec + N/2) mod N);
-      // frequency (ky, kx) goes to [(ky + N/2) mod N][vec] times the table
-      // (in the same column order, carrying the far-field factors), so a
-      // tile writes whole runs of consecutive output columns
-      const float2* __restrict__ in = static_cast<const float2*>(a.in) + (size_t)b * n * N;
-      __syncthreads();
-      load_a_direct<C>(in, N, n, off, vec, vok, x);
-      Dft<N1, -1>::run(x);
-      write_a(t, j, x);
-      __syncthreads();
-      b_forward_all<C>(t);
-      __syncthreads();
-      if (vok) {
-        const int ocol = vec;
-        float2* __restrict__ out = a.out + (size_t)b * N * N;
-#pragma unroll 4
-        for (int ky = t.s; ky < N; ky += C::S) {
-          const float2 v = t.lds[PL::slot_of_freq(ky) * C::TP + t.v];
-          const int orow = ky + N / 2 < N ? ky + N / 2 : ky - N / 2;
-          st(out, orow * N + ocol, cmul(v, ld(a.tab, ky * N + vec)));
-        }
-      }
-      continue;
-    }
-
-    // ---- row passes: vectors are layer rows y = vec0 + v
-    __syncthreads();
-    if constexpr (SPECTRAL_IN) {
-      load_spec_rows<C>(lds, static_cast<const float2*>(a.in) + (size_t)b * n * N, vec0, nvalid);
-      __syncthreads();
-      b_inverse_all<C>(t);
-      __syncthreads();
-      read_a(t, j, x);
-      Dft<N1, 1>::run(x);
-      if constexpr (LAYER) {
-        const float2* __restrict__ ai = ACC ? a.act_in + (size_t)b * nn : nullptr;
-        float2* __restrict__ ao = (KIND == kAsRowMid && a.act_out) ? a.act_out + (size_t)b * nn : nullptr;
-        for_a_elems<C>(off, n, n, vec, vok, [&](auto k, int oi, bool in) {
-          if constexpr (KIND == kAsRowMid) {
-            const float2 u = in ? cmul(x[k.value], ld(a.mod, oi)) : c2(0.f, 0.f);
-            if (ao && in) st(ao, oi, u);
-            x[k.value] = u;
-          } else {
-            const float2 ul = in ? ld(ai, oi) : c2(0.f, 0.f);
-            acc[k.value] += ul.x * x[k.value].y - ul.y * x[k.value].x;
-            if constexpr (KIND == kAsRowBwdMid) x[k.value] = in ? cmulc(x[k.value], ld(a.mod, oi)) : c2(0.f, 0.f);
-          }
-        });
-        if constexpr (KIND == kAsRowBwdLast) continue;
-      }
-    } else {
-      if constexpr (KIND == kAsRowBwdFirst) {
-        load_seed<C, kRow>(lds, a, b, vec0, nvalid);
-      } else {
-        const size_t es = a.in_real ? sizeof(float) : sizeof(float2);
-        load_tile<C, kRow, false>(lds, static_cast<const char*>(a.in) + (size_t)b * nn * es, a.in_real != 0, n, off,
-                           Consecutive{vec0}, nvalid);
-      }
-      __syncthreads();
-      read_a(t, j, x);
-    }
-
-    if constexpr (FWD_OUT) {
-      Dft<N1, -1>::run(x);
-      write_a(t, j, x);
-      __syncthreads();
-      b_forward_all<C>(t);
-      __syncthreads();
-      store_spec_rows<C>(lds, a.out + (size_t)b * n * N, vec0, nvalid, a.spec_centred != 0);
-    } else {
-      if constexpr (KIND == kAsRowLast) add_skip<C, kRow>(a, b, vec, vok, x);
-      write_a(t, j, x);  // positions, cropped on output
-      __syncthreads();
-      if constexpr (KIND == kAsRowIfft) {
-        store_tile<C, kRow, false>(lds, a.out + (size_t)b * nn, n, off, Consecutive{vec0}, nvalid);
-      } else {  // kAsRowLast
-        tile_outputs<C, kRow>(lds, rsum, a, b, Consecutive{vec0}, nvalid, wi.tile);
-      }
-    }
-  }
-  if constexpr (ACC) {
-    float* __restrict__ dp = a.dphi_part + (size_t)wi.group * nn;
-    for_a_elems<C>(off, n, n, vec, vok, [&](auto k, int idx, bool in) {
-      if (in) st(dp, idx, acc[k.value]);
-    });
   }
 }
 
@@ -2241,35 +1944,6 @@ hipError_t launch_field_fwd_n(const FieldArgs& a, hipStream_t st) {
 }
 
 // ---------------------------------------------------------------------------
-// Helper kernels
-// ---------------------------------------------------------------------------
-
-// Column-permuted 2-D table for the angular-spectrum column pass:
-// Hp[ky][c] = inv * H[ky][kx(c)] (inv = 1/N^2 for a propagation, 1 for the
-// far-field table), c the slot of frequency kx in the row plan (the layout
-// in which row passes store x-spectra).
-template <class PL>
-__global__ void prep_as_table_kernel(const float2* __restrict__ H, float2* __restrict__ Hp, float inv, int centred) {
-  constexpr int N = PL::N;
-  const size_t total = (size_t)N * N;
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
-    const int ky = (int)(i / N);
-    const int c = (int)(i - (size_t)ky * N);
-    int kx;
-    if (centred) {
-      // column c holds frequency (c + N/2) mod N (the far field's centred order)
-      kx = c + N / 2 < N ? c + N / 2 : c - N / 2;
-    } else {
-      // slot c holds element k2 of B-item k1
-      const int k1 = c / PL::N2;
-      const int k2 = c - k1 * PL::N2;
-      kx = PL::freq(k1, k2);
-    }
-    Hp[i] = cscale(H[(size_t)ky * N + kx], inv);
-  }
-}
-
-// ---------------------------------------------------------------------------
 // Per-size launchers (explicitly instantiated in one translation unit per size)
 // ---------------------------------------------------------------------------
 
@@ -2482,39 +2156,6 @@ hipError_t launch_fr_n(PassKind kind, Axis axis, const PassArgs& a, hipStream_t 
     case kBwdLast: return launch_fr_axis<N, kBwdLast>(axis, a, st);
   }
   return hipErrorInvalidValue;
-}
-
-template <int N, int KIND>
-hipError_t launch_as(const PassArgs& a, hipStream_t st) {
-  using C = std::conditional_t<KIND == kAsCol || KIND == kAsColFar, CfgFor<N>, RowCfgFor<N>>;
-  const dim3 grid(work_grid(a.ntiles, (a.batch + a.spg - 1) / a.spg));
-  hipLaunchKernelGGL((as_pass<C, KIND>), grid, dim3(C::P), 0, st, a);
-  return hipGetLastError();
-}
-
-template <int N>
-hipError_t launch_as_n(AsPassKind kind, const PassArgs& a, hipStream_t st) {
-  switch (kind) {
-    case kAsRowFirst: return launch_as<N, kAsRowFirst>(a, st);
-    case kAsCol: return launch_as<N, kAsCol>(a, st);
-    case kAsRowMid: return launch_as<N, kAsRowMid>(a, st);
-    case kAsRowLast: return launch_as<N, kAsRowLast>(a, st);
-    case kAsRowBwdFirst: return launch_as<N, kAsRowBwdFirst>(a, st);
-    case kAsRowBwdMid: return launch_as<N, kAsRowBwdMid>(a, st);
-    case kAsRowBwdLast: return launch_as<N, kAsRowBwdLast>(a, st);
-    case kAsRowIfft: return launch_as<N, kAsRowIfft>(a, st);
-    case kAsColFar: return launch_as<N, kAsColFar>(a, st);
-  }
-  return hipErrorInvalidValue;
-}
-
-template <int N>
-hipError_t prep_as_n(const float2* H, float2* Hp, float scale, int centred, hipStream_t st) {
-  if (centred && (N & 1)) return hipErrorInvalidValue;
-  const int blocks = (int)(((size_t)N * N + 255) / 256);
-  hipLaunchKernelGGL((prep_as_table_kernel<typename RowPlanFor<N>::type>), dim3(blocks < 4096 ? blocks : 4096), dim3(256),
-                     0, st, H, Hp, scale, centred);
-  return hipGetLastError();
 }
 
 template <int N>
