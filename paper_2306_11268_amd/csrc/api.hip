@@ -170,6 +170,9 @@ struct Layout {
 
 int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
+// The separable path alternates axes: pass p (1-based) runs along rows for odd p.
+Axis pass_axis(int p) { return (p & 1) ? lr::kRow : lr::kCol; }
+
 Layout make_layout(const lr_donn* net, int batch, int op) {
   Layout L;
   const int n = net->n;
@@ -204,7 +207,12 @@ Layout make_layout(const lr_donn* net, int batch, int op) {
     L.row_perm = take(static_cast<size_t>(n) * 4);
     L.col_perm = take(static_cast<size_t>(n) * 4);
   }
-  if (op == LR_OP_FORWARD && K > 0) L.sums_part = take(static_cast<size_t>(batch) * L.ntiles_vec * K * 4);
+  if (op == LR_OP_FORWARD && K > 0) {
+    // (the detector-plane pass has its own tiles, of at least one vector)
+    const int tiles = as ? L.ntiles_vec
+                         : ceil_div(n, lr::fresnel_pass_tile(N, lr::kFwdLast, pass_axis(net->num_layers + 2), n == N));
+    L.sums_part = take(static_cast<size_t>(batch) * std::max(tiles, L.ntiles_vec) * K * 4);
+  }
   if (op == LR_OP_BACKWARD) {
     if (K > 0) L.grad_sums = take(static_cast<size_t>(batch) * K * 4);
     const int work_tiles = L.ntiles_vec;
@@ -231,14 +239,12 @@ T* at(void* base, size_t off) {
   return reinterpret_cast<T*>(static_cast<char*>(base) + off);
 }
 
-// The separable path alternates axes: pass p (1-based) runs along rows for odd p.
-Axis pass_axis(int p) { return (p & 1) ? lr::kRow : lr::kCol; }
 // Layer l (1-based) is modulated in pass l+1: transposed storage when that pass is a row pass,
-// except on the wide row tiles of the 500-point plan (full aperture), which read rows.
-int layer_transposed(const lr_donn* net, int l) {
+// except where those passes take row-major tables (full aperture, the longer plans).
+int layer_transposed(const lr_donn* net, int l, bool backward) {
   if (net->approx != LR_FRESNEL) return 0;
   if (pass_axis(l + 1) != lr::kRow) return 0;
-  return lr::wide_row_tiles(net->n_fft) && net->n == net->n_fft ? 0 : 1;
+  return net->n == net->n_fft && lr::row_major_rows(net->n_fft, backward) ? 0 : 1;
 }
 
 const char* kind_name(int k) {
@@ -336,7 +342,9 @@ PassArgs base_args(const lr_donn* net, int batch) {
   a.batch = batch;
   a.spg = 1;
   a.tab_sym = net->approx == LR_ANGULAR_SPECTRUM || net->approx == LR_FRAUNHOFER ? 1 : 0;
-  a.scale = static_cast<float>(1.0 / (static_cast<double>(net->n_fft) * net->n_fft));
+  const double inv = 1.0 / (static_cast<double>(net->n_fft) * net->n_fft);
+  a.scale = static_cast<float>(inv);
+  a.scale_lo = static_cast<float>(inv - a.scale);
   return a;
 }
 
@@ -415,9 +423,9 @@ int prep_chirps(const lr_donn* net, const Layout& L, void* w, hipStream_t st) {
 // Per-call tables of a forward or backward pass in one launch: the modulation
 // of every layer, the Fresnel chirps, and (when the call reads detector
 // regions) the region tables.
-int prep_layers(const lr_donn* net, const float* d_phi, bool regions, const Layout& L, void* w, hipStream_t st) {
+int prep_layers(const lr_donn* net, const float* d_phi, bool backward, bool regions, const Layout& L, void* w, hipStream_t st) {
   int orient[LR_MAX_LAYERS];
-  for (int l = 0; l < net->num_layers; ++l) orient[l] = layer_transposed(net, l + 1);
+  for (int l = 0; l < net->num_layers; ++l) orient[l] = layer_transposed(net, l + 1, backward);
   const bool with_regions = regions && net->det.num > 0;
   const lr::Regions r = host_regions(net->det);
   const bool fresnel = net->approx == LR_FRESNEL;
@@ -803,12 +811,11 @@ int lr_donn_forward(const lr_donn* net, int32_t batch, const float* d_amp, const
   float2* ws_mod = at<float2>(d_work, L.mod);
   float2* w[2] = {at<float2>(d_work, L.w0), at<float2>(d_work, L.w1)};
 
-  LR_TRY(prep_layers(net, d_phi, d_sums != nullptr, L, d_work, st));
+  LR_TRY(prep_layers(net, d_phi, false, d_sums != nullptr, L, d_work, st));
 
   PassArgs a = base_args(net, batch);
   a.accumulate = accumulate ? 1 : 0;
   a.full = slot_ordered(net) ? 1 : 0;
-  const int tile_t = lr::tile_shape(N, 0).T;
   int sum_tiles = L.ntiles_vec;  // tiles that wrote partial detector sums
   const bool whole_field = net->approx == LR_FRESNEL && n == N && lr::field_forward_supported(N) &&
                            ((net->flags & LR_WHOLE_FIELD) || lr::field_forward_preferred(N, batch)) && !saved &&
@@ -821,7 +828,7 @@ int lr_donn_forward(const lr_donn* net, int32_t batch, const float* d_amp, const
     fa.amp = d_amp;
     fa.mod = ws_mod;
     for (int l = 1; l <= Lyr; ++l)
-      if (layer_transposed(net, l)) fa.mod_t |= 1ull << (l - 1);
+      if (layer_transposed(net, l, false)) fa.mod_t |= 1ull << (l - 1);
     fa.layers = Lyr;
     fa.chirp_x = at<float2>(d_work, L.chirp_x);
     fa.chirp_y = at<float2>(d_work, L.chirp_y);
@@ -863,7 +870,9 @@ int lr_donn_forward(const lr_donn* net, int32_t batch, const float* d_amp, const
     // pass L+1: rest of hop L+1, detector plane
     if (d_sums || d_intensity || d_field_out) {
       const Axis ax = pass_axis(Lyr + 2);
+      const int tile_t = lr::fresnel_pass_tile(N, lr::kFwdLast, ax, a.full != 0);
       PassArgs d = a;
+      d.ntiles = ceil_div(n, tile_t);
       d.in = a.out;
       d.out = nullptr;
       d.tab = chirp(ax);
@@ -975,7 +984,7 @@ int lr_donn_backward(const lr_donn* net, int32_t batch, const float* d_phi, cons
   float2* w[2] = {at<float2>(d_work, L.w0), at<float2>(d_work, L.w1)};
   float* part = at<float>(d_work, L.dphi_part);
 
-  LR_TRY(prep_layers(net, d_phi, d_labels || d_grad_sums, L, d_work, st));
+  LR_TRY(prep_layers(net, d_phi, true, d_labels || d_grad_sums, L, d_work, st));
   const float* gsum = d_grad_sums;
   if (d_labels) {
     float* g = at<float>(d_work, L.grad_sums);
@@ -995,7 +1004,7 @@ int lr_donn_backward(const lr_donn* net, int32_t batch, const float* d_phi, cons
   auto part_of = [&](int l) { return part + static_cast<size_t>(l - 1) * layer_stride; };
   int groups_of[LR_MAX_LAYERS] = {};
   int orient_of[LR_MAX_LAYERS] = {};
-  for (int l = 1; l <= Lyr; ++l) orient_of[l - 1] = layer_transposed(net, l);
+  for (int l = 1; l <= Lyr; ++l) orient_of[l - 1] = layer_transposed(net, l, true);
   auto reduce_all = [&]() {
     return run_timed("reduce_dphi", st, [&] {
       return lr::launch_reduce_dphi(part, layer_stride, groups_of, orient_of, Lyr, n, slot_map_of(net), d_grad_phi,
@@ -1015,12 +1024,14 @@ int lr_donn_backward(const lr_donn* net, int32_t batch, const float* d_phi, cons
       s.grad_int = d_grad_intensity;
       s.grad_sums = gsum;
       s.skip = reinterpret_cast<const float2*>(net->d_skip);
+      const int tile_t = lr::fresnel_pass_tile(N, lr::kBwdFirst, ax, a.full != 0);
+      s.ntiles = ceil_div(n, tile_t);
       if (gsum) {
         set_detector(s, net->det, L, d_work);
         // The seed vanishes off the covered rows (columns).  A row seed pass
         // leaves the other rows unwritten, and the next (column) pass skips
         // them; a column seed pass writes zero columns for the row pass after it.
-        restrict_to_regions(s, net->det, L, d_work, ax, lr::tile_shape(N, 0).T, ax == lr::kCol);
+        restrict_to_regions(s, net->det, L, d_work, ax, tile_t, ax == lr::kCol);
         if (ax == lr::kRow) live_rows = at<unsigned long long>(d_work, L.row_mask);
       }
       s.out = w[0];

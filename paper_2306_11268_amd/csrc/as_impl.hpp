@@ -31,180 +31,18 @@
 // the A-step runs HalfDft, and half of the loads, stores and products vanish.
 #pragma once
 
+#include "exchange.hpp"
 #include "kernels_impl.hpp"
 
 namespace lr {
 
-// Barrier between shared-memory phases of a workgroup of P threads.  One wave
-// needs no hardware barrier and no wait: its shared-memory accesses complete
-// in order, so only the compiler has to keep them in order.
-template <int P>
-__device__ __forceinline__ void exchange_sync() {
-  if constexpr (P == 64) {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  } else {
-    __syncthreads();
-  }
-}
-
-// Rounds of B-items per lane (item k1 = s + N2*ic in round ic).
 template <class PL, bool FENCED = false>
-struct AsItems {
-  using Plan = PL;
-  static constexpr int N = PL::N;
-  static constexpr int N1 = PL::N1;
-  static constexpr int N2 = PL::N2;
-  static constexpr int IB = (N1 + N2 - 1) / N2;
-  static constexpr bool FULL_ROUNDS = N1 % N2 == 0;
-  static constexpr int P1 = N2 + 1;  // exchange pitch of a B-item
-  static constexpr bool LONG = FENCED || N1 > 16 || N2 * IB > 16;
-  static_assert(!PL::PFA && N2 % 2 == 0, "natural order and an odd exchange pitch");
-  // Whether lane s has an item in round ic, and the item it works on: row
-  // passes (REPEAT) let a lane past the last item repeat one of that round's
-  // items, the same values from and to the same shared-memory entries, because
-  // a branch around the item kept the compiler from scheduling the arrays live
-  // across it (100-400 bytes of scratch); column passes, where whole waves are
-  // past the last item, branch (500 points: 54 us against 106 with repeats).
-  static __device__ __forceinline__ bool item(int s, int ic) { return FULL_ROUNDS || s + N2 * ic < N1; }
-  template <bool REPEAT>
-  static __device__ __forceinline__ int item_of(int s, int ic) {
-    constexpr int last = N1 - N2 * (IB - 1);  // items of the last round
-    return N2 * ic + (!REPEAT || FULL_ROUNDS || ic + 1 < IB ? s : s % last);
-  }
-  static constexpr int K0(bool half) { return half ? N1 / 4 : 0; }
-  static constexpr int KN(bool half) { return half ? N1 / 2 : N1; }  // elements of an A-item in the aperture (HALF) or all
+struct AsItems : Items<PL, FENCED> {
+  static_assert(!PL::PFA, "natural order");
+  // elements of an A-item inside a half aperture (HALF), or all of them
+  static constexpr int K0(bool half) { return half ? PL::N1 / 4 : 0; }
+  static constexpr int KN(bool half) { return half ? PL::N1 / 2 : PL::N1; }
 };
-
-// Exchange of one vector's A-item (x) with its B-items (y).  The A side of
-// element k1 is buf[ab + SA*k1], the B side of element q of round ic
-// buf[bb[ic] + SQ*q].  Each lane rewrites only entries it read last, so
-// successive exchanges need no barrier between them.  SPLIT: one component
-// at a time through a float buffer (half the shared memory, three times the
-// barriers), else a float2 buffer.  s: the lane's slot (A-item).
-template <class IT, int P, bool SPLIT, bool REPEAT, int SA, int SQ>
-struct AsExchange {
-  using Elem = std::conditional_t<SPLIT, float, float2>;
-  static constexpr int N1 = IT::N1;
-  static constexpr int N2 = IT::N2;
-  static constexpr int IB = IT::IB;
-  static __device__ __forceinline__ bool has(int s, int ic) { return REPEAT || IT::item(s, ic); }
-  static __device__ __forceinline__ void to_items(Elem* buf, int s, int ab, const int (&bb)[IB], const float2 (&x)[N1],
-                                                  float2 (&y)[IB][N2]) {
-    if constexpr (SPLIT) {
-      static_for<0, 2>([&](auto c) {
-        static_for<0, N1>([&](auto k) { buf[ab + SA * k.value] = c.value ? x[k.value].y : x[k.value].x; });
-        exchange_sync<P>();
-        static_for<0, IB>([&](auto ic) {
-          if (!has(s, ic.value)) return;
-          static_for<0, N2>([&](auto q) {
-            const float v = buf[bb[ic.value] + SQ * q.value];
-            if constexpr (c.value) y[ic.value][q.value].y = v; else y[ic.value][q.value].x = v;
-          });
-        });
-        if constexpr (c.value == 0) exchange_sync<P>();
-      });
-    } else {
-      static_for<0, N1>([&](auto k) { buf[ab + SA * k.value] = x[k.value]; });
-      exchange_sync<P>();
-      static_for<0, IB>([&](auto ic) {
-        if (!has(s, ic.value)) return;
-        static_for<0, N2>([&](auto q) { y[ic.value][q.value] = buf[bb[ic.value] + SQ * q.value]; });
-      });
-    }
-    // lanes that repeat an item read entries another lane rewrites next
-    if constexpr (REPEAT && !IT::FULL_ROUNDS) exchange_sync<P>();
-  }
-  static __device__ __forceinline__ void to_vector(Elem* buf, int s, int ab, const int (&bb)[IB], const float2 (&y)[IB][N2],
-                                                   float2 (&x)[N1]) {
-    if constexpr (SPLIT) {
-      static_for<0, 2>([&](auto c) {
-        static_for<0, IB>([&](auto ic) {
-          if (!has(s, ic.value)) return;
-          static_for<0, N2>([&](auto q) {
-            buf[bb[ic.value] + SQ * q.value] = c.value ? y[ic.value][q.value].y : y[ic.value][q.value].x;
-          });
-        });
-        exchange_sync<P>();
-        static_for<0, N1>([&](auto k) {
-          const float v = buf[ab + SA * k.value];
-          if constexpr (c.value) x[k.value].y = v; else x[k.value].x = v;
-        });
-        if constexpr (c.value == 0) exchange_sync<P>();
-      });
-    } else {
-      static_for<0, IB>([&](auto ic) {
-        if (!has(s, ic.value)) return;
-        static_for<0, N2>([&](auto q) { buf[bb[ic.value] + SQ * q.value] = y[ic.value][q.value]; });
-      });
-      exchange_sync<P>();
-      static_for<0, N1>([&](auto k) { x[k.value] = buf[ab + SA * k.value]; });
-    }
-  }
-};
-
-// Long items (more than 16 values of a vector or of its items per lane): an
-// index goes through an empty asm statement, so that roots and addresses
-// derived from it are formed next to their use, not hoisted and kept live, and
-// scheduling barriers between the phases of a pass do the same for loads.
-// Short items have the registers, and their root and table loads are better
-// in flight early (64 points: column pass 14.7 -> 13.6 us); in the persistent
-// kinds (FENCED) they too would be kept live across the samples (256 points,
-// adjoint row pass 46 -> 60 us).
-template <class IT>
-__device__ __forceinline__ int opaque(int v) {
-  if constexpr (IT::LONG) asm volatile("" : "+v"(v));
-  return v;
-}
-template <class IT>
-__device__ __forceinline__ void phase() {
-  if constexpr (IT::LONG) __builtin_amdgcn_sched_barrier(0);
-}
-
-// Cooley-Tukey twiddles exp(-+2*pi*i*k1*j/N) of a B-item, eight at a time so
-// that their roots and products are not all live at once.  Items of 32 or
-// more: w^(k1*j) = w^(k1*(j mod 8)) * w^(8*k1*(j/8)), one more rounding
-// (<= 1.5 ulp) for 7 + N2/8 - 1 loads instead of N2 - 1.
-template <class IT, bool INV>
-__device__ __forceinline__ void as_twiddle(int k1, float2 (&y)[IT::N2]) {
-  constexpr int N2 = IT::N2;
-  auto root = [&](int m) { return root_at<IT::N>(INV ? (unsigned)(IT::N - k1 * m) : (unsigned)(k1 * m)); };
-  if constexpr (N2 >= 32) {
-    float2 lo[8];
-    static_for<1, 8>([&](auto i) { lo[i.value] = root(i.value); });
-    static_for<0, N2 / 8>([&](auto bc) {
-      constexpr int b = decltype(bc)::value;
-      if constexpr (b == 0) {
-        static_for<1, 8>([&](auto i) { y[i.value] = cmul(y[i.value], lo[i.value]); });
-      } else {
-        const float2 hi = root(8 * b);
-        y[8 * b] = cmul(y[8 * b], hi);
-        static_for<1, 8>([&](auto i) { y[8 * b + i.value] = cmul(y[8 * b + i.value], cmul(lo[i.value], hi)); });
-      }
-      phase<IT>();
-    });
-  } else {
-    static_for<1, N2>([&](auto j) {
-      y[j.value] = cmul(y[j.value], root(j.value));
-      if constexpr (j.value % 8 == 7) phase<IT>();
-    });
-  }
-}
-template <class IT>
-__device__ __forceinline__ void as_b_forward(int k1, float2 (&y)[IT::N2]) {
-  as_twiddle<IT, false>(opaque<IT>(k1), y);
-  phase<IT>();
-  Dft<IT::N2, -1>::run(y);
-  phase<IT>();
-}
-template <class IT>
-__device__ __forceinline__ void as_b_inverse(int k1, float2 (&y)[IT::N2]) {
-  Dft<IT::N2, 1>::run(y);
-  phase<IT>();
-  as_twiddle<IT, true>(opaque<IT>(k1), y);
-  phase<IT>();
-}
 
 // A-step of the elements u[0..KN) a lane holds (HALF: the middle half).
 template <class IT, bool HALF>
@@ -236,8 +74,9 @@ __device__ __forceinline__ void as_a_inverse(float2 (&x)[IT::N1], float2 (&u)[IT
 template <class PL>
 struct AsRows : AsItems<PL> {
   using IT = AsItems<PL>;
-  static constexpr int R = IT::N2 <= 32 ? 64 / IT::N2 : 8;
+  static constexpr int R = (IT::N2 <= 32 ? 64 : 256) / IT::N2;
   static constexpr int P = (R * IT::N2 + 63) / 64 * 64;
+  static constexpr bool SPARE = P != R * IT::N2 && P > 64;
   // row pitch: at least the exchange area, and = N2 mod 64, so that the rows
   // of a wave tile the banks on the A side
   static constexpr int PR = IT::N1 * IT::P1 + (64 + IT::N2 - IT::N1 * IT::P1 % 64) % 64;
@@ -257,7 +96,7 @@ __global__ void __launch_bounds__(AsRows<PL>::P, (KIND == kAsRowBwdMid || KIND =
     as_row_pass(PassArgs a) {
   using W = AsRows<PL>;
   using IT = AsItems<PL, KIND == kAsRowBwdMid || KIND == kAsRowBwdLast>;
-  using EX = AsExchange<IT, W::P, W::SPLIT, true, W::P1, 1>;
+  using EX = Exchange<IT, W::P, W::SPLIT, true, W::SPARE, W::P1, 1>;
   constexpr int N = W::N;
   constexpr int N1 = W::N1;
   constexpr int N2 = W::N2;
@@ -274,18 +113,21 @@ __global__ void __launch_bounds__(AsRows<PL>::P, (KIND == kAsRowBwdMid || KIND =
   const int rank = (int)blockIdx.x;
   if (rank >= a.workers) return;
   const int tid = (int)threadIdx.x;
-  // the lanes past the R rows repeat the first items of row 0 (the same values
-  // to the same shared-memory entries, no branch) and store nothing
+  // the lanes past the R rows store nothing: in a one-wave workgroup they repeat
+  // the first items of row 0 (the same values to the same shared-memory
+  // entries, no branch); else (SPARE) their A side is the exchange area's
+  // padding column and on the B side they repeat item 0
   const bool act = R * N2 == W::P || tid < R * N2;
   const int r = act ? tid / N2 : 0;
-  const int j0 = act ? tid - r * N2 : tid - R * N2;
+  const int j0 = act ? tid - r * N2 : (W::SPARE ? N2 : tid - R * N2);
+  const int s0 = W::SPARE && !act ? 0 : j0;
   const int n = a.n;
   const int off = a.off;
   const size_t nn = (size_t)n * n;
   const int total = a.ntiles * a.batch;
   const int ab = r * W::PR + j0;
   int bb[IB];
-  static_for<0, IB>([&](auto ic) { bb[ic.value] = r * W::PR + W::P1 * IT::template item_of<true>(j0, ic.value); });
+  static_for<0, IB>([&](auto ic) { bb[ic.value] = r * W::PR + W::P1 * IT::template item_of<true>(s0, ic.value); });
 
   float acc[ACC ? KN : 1];
   if constexpr (ACC) {
@@ -296,8 +138,9 @@ __global__ void __launch_bounds__(AsRows<PL>::P, (KIND == kAsRowBwdMid || KIND =
     const int tile = it % a.ntiles;
     const int b = it / a.ntiles;
     const int j = opaque<IT>(j0);
+    const int s = opaque<IT>(s0);
     const int vec = tile * R + r;
-    const bool vok = vec < n;
+    const bool vok = vec < n && (!W::SPARE || act);
     auto pos_ok = [&](int jj, auto k) { return HALF || (unsigned)(jj + N2 * decltype(k)::value - off) < (unsigned)n; };
     // f(k, byte offset per lane, scalar byte offset) for the elements of this
     // lane's A-item in an n x n natural array of es-byte values; the per-lane
@@ -318,7 +161,7 @@ __global__ void __launch_bounds__(AsRows<PL>::P, (KIND == kAsRowBwdMid || KIND =
     auto each_out = [&](int es, auto&& f) { each_if(vok && act, es, f); };
     // spectrum element (round ic, k2) of this row: frequency k1 + N1*k2
     auto spec_base = [&](bool ok, int ic) -> unsigned {
-      return ok ? (unsigned)(vec * N + IT::template item_of<true>(j, ic)) * 8u : kOutOfRange;
+      return ok ? (unsigned)(vec * N + IT::template item_of<true>(s, ic)) * 8u : kOutOfRange;
     };
     if constexpr (KIND == kAsRowLast) {
       // sums only: rows no region covers contribute nothing
@@ -339,16 +182,16 @@ __global__ void __launch_bounds__(AsRows<PL>::P, (KIND == kAsRowBwdMid || KIND =
       const Rsrc rin = make_rsrc(static_cast<const float2*>(a.in) + (size_t)b * n * N, (unsigned)(n * N) * 8u);
       float2 y[IB][N2];
       static_for<0, IB>([&](auto ic) {
-        const unsigned base = spec_base(vok, ic.value);
+        const unsigned base = spec_base(vec < n, ic.value);
         static_for<0, N2>([&](auto k2) { y[ic.value][k2.value] = bload_so<2>(rin, base, N1 * 8 * k2.value); });
       });
-      const int ji = opaque<IT>(j);
+      const int ji = opaque<IT>(s);
       static_for<0, IB>([&](auto ic) {
-        as_b_inverse<IT>(IT::template item_of<true>(ji, ic.value), y[ic.value]);
+        item_inverse<IT>(IT::template item_of<true>(ji, ic.value), y[ic.value]);
       });
       phase<IT>();
       float2 x[N1];
-      EX::to_vector(buf, j, ab, bb, y, x);
+      EX::to_vector(buf, s, ab, bb, y, x);
       phase<IT>();
       as_a_inverse<IT, HALF>(x, u);
       phase<IT>();
@@ -412,14 +255,14 @@ __global__ void __launch_bounds__(AsRows<PL>::P, (KIND == kAsRowBwdMid || KIND =
       as_a_forward<IT, HALF>(u, x);
       phase<IT>();
       float2 y[IB][N2];
-      EX::to_items(buf, j, ab, bb, x, y);
+      EX::to_items(buf, s, ab, bb, x, y);
       phase<IT>();
-      const int jf = opaque<IT>(j);
+      const int jf = opaque<IT>(s);
       const Rsrc ro = make_rsrc(a.out + (size_t)b * n * N, (unsigned)(n * N) * 8u);
       // centred: position p holds frequency (p + N/2) mod N, a rotation of k2 by N2/2
       const int rot = a.spec_centred ? N * 4 : 0;
       static_for<0, IB>([&](auto ic) {
-        as_b_forward<IT>(IT::template item_of<true>(jf, ic.value), y[ic.value]);
+        item_forward<IT>(IT::template item_of<true>(jf, ic.value), y[ic.value]);
         const unsigned base = spec_base(vok && act && IT::item(jf, ic.value), ic.value);
         static_for<0, N2>([&](auto k2) {
           bstore_so(ro, base, N1 * 8 * k2.value + (k2.value < N2 / 2 ? rot : -rot), y[ic.value][k2.value]);
@@ -519,8 +362,10 @@ __global__ void __launch_bounds__(AsRows<PL>::P, (KIND == kAsRowBwdMid || KIND =
 template <class PL, int T>
 struct AsCols : AsItems<PL> {
   using IT = AsItems<PL>;
-  static constexpr int P = T * IT::N2;
-  static_assert(P % 64 == 0, "whole waves");
+  static constexpr int P = (T * IT::N2 + 63) / 64 * 64;
+  // the lanes past the T columns: their A side is the exchange area's padding
+  // column, on the B side they repeat item 0, and they store nothing
+  static constexpr bool SPARE = P != T * IT::N2;
   static constexpr int LDS = IT::N1 * IT::P1 * T;
   static constexpr bool PAIRS = (IT::N & (IT::N - 1)) == 0;
   static constexpr bool SPLIT = LDS * 8 > 10 * 1024 * (P / 64);  // as for the rows
@@ -531,7 +376,7 @@ template <class PL, int T, bool HALF, bool FAR>
 __global__ void __launch_bounds__((AsCols<PL, T>::P), (AsCols<PL, T>::WAVES)) as_col_pass(PassArgs a) {
   using W = AsCols<PL, T>;
   using IT = AsItems<PL>;
-  using EX = AsExchange<IT, W::P, W::SPLIT, false, W::P1 * T, T>;
+  using EX = Exchange<IT, W::P, W::SPLIT, false, W::SPARE, W::P1 * T, T>;
   constexpr int N = W::N;
   constexpr int N1 = W::N1;
   constexpr int N2 = W::N2;
@@ -557,15 +402,17 @@ __global__ void __launch_bounds__((AsCols<PL, T>::P), (AsCols<PL, T>::WAVES)) as
   }
 
   const int tid = (int)threadIdx.x;
-  const int v = tid % T;
-  const int j = tid / T;
+  const bool act = !W::SPARE || tid < T * N2;
+  const int v = (act ? tid : tid - T * N2) % T;
+  const int j = act ? tid / T : N2;
+  const int s = act ? j : 0;
   const int n = a.n;
   const int off = a.off;
   const int vec = tile * T + v;
-  const bool vok = vec < N;
+  const bool vok = vec < N && act;
   const int ab = j * T + v;
   int bb[IB];
-  static_for<0, IB>([&](auto ic) { bb[ic.value] = IT::template item_of<false>(j, ic.value) * W::P1 * T + v; });
+  static_for<0, IB>([&](auto ic) { bb[ic.value] = IT::template item_of<false>(s, ic.value) * W::P1 * T + v; });
   // f(k, byte offset per lane, scalar byte offset) of this lane's A-item: rows
   // pos - off of column vec
   auto each = [&](auto&& f) {
@@ -588,7 +435,7 @@ __global__ void __launch_bounds__((AsCols<PL, T>::P), (AsCols<PL, T>::WAVES)) as
   as_a_forward<IT, HALF>(u, x);
   phase<IT>();
   float2 y[IB][N2];
-  EX::to_items(buf, j, ab, bb, x, y);
+  EX::to_items(buf, s, ab, bb, x, y);
   phase<IT>();
 
   // rows ky = k1 + N1*k2; the mirrored row N - ky = (N1 - k1) + N1*(N2 - 1 - k2)
@@ -598,12 +445,13 @@ __global__ void __launch_bounds__((AsCols<PL, T>::P), (AsCols<PL, T>::WAVES)) as
   int kx = vec;
   if constexpr (FAR) kx = vec + N / 2 < N ? vec + N / 2 : vec - N / 2;  // centred columns
   static_for<0, IB>([&](auto ic) {
-    if (!IT::item(j, ic.value)) return;
-    const int k1 = j + N2 * ic.value;
+    if (!IT::item(s, ic.value)) return;
+    const int k1 = s + N2 * ic.value;
     float2(&z)[N2] = y[ic.value];
-    as_b_forward<IT>(k1, z);
-    const unsigned lo = vok ? (unsigned)(k1 * N + kx) * 8u : kOutOfRange;
-    const unsigned hi = vok && sym ? (unsigned)((N1 - k1) * N + kx) * 8u : lo;
+    item_forward<IT>(k1, z);
+    const bool col = vec < N;  // (spare lanes repeat an item, table and all)
+    const unsigned lo = col ? (unsigned)(k1 * N + kx) * 8u : kOutOfRange;
+    const unsigned hi = col && sym ? (unsigned)((N1 - k1) * N + kx) * 8u : lo;
     static_for<0, N2>([&](auto k2) {
       constexpr int up = N1 * N * 8 * decltype(k2)::value;
       constexpr int down = N1 * N * 8 * (N2 - 1 - decltype(k2)::value);
@@ -620,26 +468,35 @@ __global__ void __launch_bounds__((AsCols<PL, T>::P), (AsCols<PL, T>::WAVES)) as
       });
     } else {
       phase<IT>();
-      as_b_inverse<IT>(k1, z);
+      item_inverse<IT>(k1, z);
     }
   });
   if constexpr (!FAR) {
-    EX::to_vector(buf, j, ab, bb, y, x);
+    EX::to_vector(buf, s, ab, bb, y, x);
     phase<IT>();
     as_a_inverse<IT, HALF>(x, u);
     const Rsrc ro = make_rsrc(a.out + (size_t)b * n * N, (unsigned)(n * N) * 8u);
-    each([&](auto k, unsigned o, int so) { bstore_so(ro, o, so, cscale(u[k.value], a.scale)); });
+    // 1/N^2 is a power of two or carries its rounding error along: the same
+    // factor in every hop, an error of up to 2.5e-8 would add up over them
+    auto scaled = [&](float v) { return (N & (N - 1)) == 0 ? v * a.scale : fmaf(v, a.scale, v * a.scale_lo); };
+    each([&](auto k, unsigned o, int so) {
+      bstore_so(ro, o, so, c2(scaled(u[k.value].x), scaled(u[k.value].y)));
+    });
   }
 }
 
-// Columns per workgroup: whole waves of T * N2 threads, and 128-byte segments
-// of every row (at 1024 points 8 columns, four waves instead of eight per
-// workgroup, measured 181 against 156 us for 64 samples of 512 rows, at 1000
-// 54.8 against 44.5 us for 8 of 1000; 32 columns at 256 and 512 5% slower).
+// Columns per workgroup: 128-byte segments of every row (at 1024 points 8
+// columns, four waves instead of eight, measured 181 against 156 us for 64
+// samples of 512 rows; 32 columns at 256 and 512 5% slower), more where that
+// would not be whole waves; at 100, 200 and 500 points, whose rows do not end
+// on 128-byte lines, as many as fill 256 lanes (a five-wave workgroup leaves
+// SIMDs uneven, sep_impl.hpp): 200 points 48 -> 41 us for 200 samples, 250 in
+// 500 47 -> 37 us for 32 (at 400, whose rows do, 45 -> 54 us, so not there).
 template <int N> struct AsColT { static constexpr int T = 16; };
-template <> struct AsColT<100>  { static constexpr int T = 32; };
-template <> struct AsColT<200>  { static constexpr int T = 32; };
-template <> struct AsColT<350>  { static constexpr int T = 32; };
+template <> struct AsColT<100> { static constexpr int T = 25; };
+template <> struct AsColT<200> { static constexpr int T = 25; };
+template <> struct AsColT<350> { static constexpr int T = 32; };
+template <> struct AsColT<500> { static constexpr int T = 12; };
 
 // n = N/2 centred and N1 divisible by 4: HalfDft.
 template <int N>
@@ -673,11 +530,11 @@ hipError_t launch_as_col(const PassArgs& args, hipStream_t st) {
   const dim3 grid(8 * ((a.workers + 7) / 8));
   if constexpr (as_half_plan<N>()) {
     if (as_half<N>(a)) {
-      hipLaunchKernelGGL((as_col_pass<PL, T, true, FAR>), grid, dim3(T * PL::N2), 0, st, a);
+      hipLaunchKernelGGL((as_col_pass<PL, T, true, FAR>), grid, dim3(AsCols<PL, T>::P), 0, st, a);
       return hipGetLastError();
     }
   }
-  hipLaunchKernelGGL((as_col_pass<PL, T, false, FAR>), grid, dim3(T * PL::N2), 0, st, a);
+  hipLaunchKernelGGL((as_col_pass<PL, T, false, FAR>), grid, dim3(AsCols<PL, T>::P), 0, st, a);
   return hipGetLastError();
 }
 

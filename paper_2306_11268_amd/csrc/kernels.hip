@@ -15,6 +15,7 @@ template <int N> int as_rows_n();
 template <int N> int slots_as_n(AsPassKind, bool);
 template <int N> TileShape shape_n();
 template <int N> SlotMap slot_map_n();
+template <int N> bool row_major_n(bool);
 template <int N> hipError_t launch_field_fwd_n(const FieldArgs&, hipStream_t);
 
 // ---------------------------------------------------------------------------
@@ -465,7 +466,22 @@ SlotMap slot_map(int N) {
   }
 }
 
-bool wide_row_tiles(int N) { return N == 500; }
+bool row_major_rows(int N, bool backward) {
+  switch (N) {
+    case 64: return row_major_n<64>(backward);
+    case 100: return row_major_n<100>(backward);
+    case 128: return row_major_n<128>(backward);
+    case 200: return row_major_n<200>(backward);
+    case 256: return row_major_n<256>(backward);
+    case 350: return row_major_n<350>(backward);
+    case 400: return row_major_n<400>(backward);
+    case 500: return row_major_n<500>(backward);
+    case 512: return row_major_n<512>(backward);
+    case 1000: return row_major_n<1000>(backward);
+    case 1024: return row_major_n<1024>(backward);
+    default: return false;
+  }
+}
 
 bool field_forward_supported(int N) { return N == 64 || N == 100 || N == 128 || N == 200; }
 

@@ -59,7 +59,8 @@ struct PassArgs {
   // transfer function H[ky][kx] (angular-spectrum path)
   const float2* tab;
   int conj_tab;
-  float scale;    // angular-spectrum column pass: factor of its output (1/N^2)
+  float scale;    // angular-spectrum column pass: factor of its output, 1/N^2 = scale + scale_lo
+  float scale_lo;
   // modulation gamma*exp(j*phi_l), oriented [q][vec] (separable path) or natural [y][x]
   const float2* mod;
   int conj_mod;
@@ -158,10 +159,10 @@ struct FieldArgs {
   int accumulate;              // intensity is added to the output
   int batch;
 };
-// Whether the row layer passes of this FFT length run on the wide row tiles
-// (wide_row_pass, N = 500, full aperture), whose modulation tables and dphi
-// partials are [row][col] instead of the row passes' [col][row].
-bool wide_row_tiles(int N);
+// Whether the row layer passes of a forward or backward call at this FFT length
+// (full aperture) take their modulation tables and dphi partials as [row][col]
+// (sep_pass) instead of the tile passes' [col][row].
+bool row_major_rows(int N, bool backward);
 bool field_forward_supported(int N);
 // Whether a forward call of this size and batch should take the whole-field
 // kernel: it runs one sample per workgroup, so below one sample per CU it

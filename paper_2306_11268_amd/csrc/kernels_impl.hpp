@@ -975,9 +975,9 @@ __global__ void __launch_bounds__(C::P, C::WAVES) detector_pass(PassArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Wave-tile layer passes: the layer kinds of the separable path for a field
-// stored in slot order (FULL) with a plan whose B-step has N2 = 8 points
-// (N = 64, 128, 200).
+// Wave-tile layer pass: the forward layer kind of the separable path for a
+// field stored in slot order (FULL) with a plan whose B-step has N2 = 8 points
+// (N = 200).
 //
 // A workgroup is one wave and transforms 8 vectors.  Lane (v, j) holds A-item
 // j of vector vec0 + v in registers: its N1 elements at the stored indices
@@ -1082,19 +1082,17 @@ template <int N, int ES, bool QMAJOR, int K>
 constexpr int wt_soff() { return QMAJOR ? K * 8 * N * ES : K * 8 * ES; }
 
 template <class PL, int KIND, int AXIS>
-__global__ void __launch_bounds__(64, (KIND == kBwdMid || KIND == kBwdLast) ? 3 : 4) wave_pass(PassArgs a) {
+__global__ void __launch_bounds__(64, 4) wave_pass(PassArgs a) {
   using WT = WaveTile<PL, AXIS>;
   constexpr int N = PL::N;
   constexpr int N1 = PL::N1;
-  constexpr bool ACC = (KIND == kBwdMid || KIND == kBwdLast);
   constexpr bool FQ = AXIS == kCol;  // field arrays q-major along this pass
-  static_assert(KIND == kFwdMid || ACC, "wave tiles run the layer kinds");
+  static_assert(KIND == kFwdMid, "wave tiles run the forward layer pass");
   // chirp entries of B-item k1 at 9*k1 + k2: the 8 B-items a wave reads at
   // once then start in 8 different bank pairs (a pitch of 8 put two of them
   // on each pair)
   __shared__ float2 tab[9 * N1];
   __shared__ float2 xch[WT::XCH];
-  __shared__ float acc_lds[ACC ? N1 * 64 : 1];  // per-lane dphi accumulators
 
   const int G = (int)gridDim.x;
   const int l = (int)blockIdx.x;
@@ -1109,9 +1107,6 @@ __global__ void __launch_bounds__(64, (KIND == kBwdMid || KIND == kBwdLast) ? 3 
 
   // chirp in B-item order: entry 9*k1 + k2 is frequency freq(k1, k2)
   for (int i = lane; i < N; i += 64) tab[i + (i >> 3)] = a.tab[PL::freq(i >> 3, i & 7)];
-  if constexpr (ACC) {
-    static_for<0, N1>([&](auto k) { acc_lds[k.value * 64 + lane] = 0.f; });
-  }
 
   // One 1-D propagation of this lane's A-item: A-step DFT, B-step (DFT,
   // x chirp, inverse DFT) in chunks of 8 B-items through the exchange
@@ -1175,18 +1170,6 @@ __global__ void __launch_bounds__(64, (KIND == kBwdMid || KIND == kBwdLast) ? 3 
   };
   auto nothing = [] {};
 
-  // rows of G that can be nonzero (layer L of a region loss, column passes)
-  unsigned gmask = ~0u;
-  if constexpr (ACC && AXIS == kCol) {
-    if (a.live) {
-      gmask = 0u;
-      const int j = WT::j_of(lane);
-      static_for<0, N1>([&](auto k) {
-        if (ld(a.live, PL::pos_of_slot(j + 8 * k.value)) != 0ull) gmask |= 1u << k.value;
-      });
-    }
-  }
-
   for (int it = rank; it < total; it += a.workers) {
     const int tile = it % a.ntiles;
     const int b = it / a.ntiles;
@@ -1197,280 +1180,23 @@ __global__ void __launch_bounds__(64, (KIND == kBwdMid || KIND == kBwdLast) ? 3 
     const unsigned tb = wt_base<N, 8, true>(j, vec, vok);  // [q][vec] tables
     const Rsrc rin = make_rsrc(static_cast<const float2*>(a.in) + (size_t)b * nn, (unsigned)nn * 8u);
     const Rsrc rmod = make_rsrc(a.mod, (unsigned)nn * 8u);
-    auto load_field = [&](Rsrc r, unsigned mask, float2(&x)[N1]) {
+    auto load_field = [&](Rsrc r, float2(&x)[N1]) {
       static_for<0, N1>([&](auto k) {
-        x[k.value] = bload_so<field_load_policy<N>()>(r, ((mask >> k.value) & 1u) ? fb : kOutOfRange,
-                                                      wt_soff<N, 8, FQ, k.value>());
+        x[k.value] = bload_so<field_load_policy<N>()>(r, fb, wt_soff<N, 8, FQ, k.value>());
       });
     };
     auto load_mod = [&](float2(&m)[N1]) {
       static_for<0, N1>([&](auto k) { m[k.value] = bload_keep_so(rmod, tb, wt_soff<N, 8, true, k.value>()); });
     };
     float2 x[N1];
-    if constexpr (KIND == kFwdMid) {
-      load_field(rin, ~0u, x);
-      float2 m[N1];
-      prop(x, a.conj_tab != 0, nothing);
-      load_mod(m);
-      static_for<0, N1>([&](auto k) { x[k.value] = cmul(x[k.value], m[k.value]); });
-      prop(x, a.conj_tab != 0, nothing);
-    } else {
-      const Rsrc rw = make_rsrc(a.act_in + (size_t)b * nn, (unsigned)nn * 8u);
-      float2 ar[N1];
-      float2 m[N1];
-      if constexpr (KIND == kBwdMid) {
-        // A_l from the saved input of the forward pass, then the gradient
-        load_field(rw, ~0u, ar);
-        load_field(rin, gmask, x);
-        prop(ar, false, nothing);
-        prop(x, true, nothing);
-      } else {
-        load_field(rin, gmask, x);
-        load_field(rw, ~0u, ar);
-        prop(x, true, nothing);
-        prop(ar, false, nothing);
-      }
-      load_mod(m);
-      // h = conj(M_l) G_l and dphi_l += Im(conj(A_l) h)
-      static_for<0, N1>([&](auto k) {
-        const float2 h = cmulc(x[k.value], m[k.value]);
-        acc_lds[k.value * 64 + lane] += ar[k.value].x * h.y - ar[k.value].y * h.x;
-        x[k.value] = h;
-      });
-      if constexpr (KIND == kBwdMid) prop(x, true, nothing);
-    }
-    if constexpr (KIND != kBwdLast) {
-      const Rsrc rout = make_rsrc(a.out + (size_t)b * nn, (unsigned)nn * 8u);
-      static_for<0, N1>([&](auto k) { bstore_so(rout, fb, wt_soff<N, 8, FQ, k.value>(), x[k.value]); });
-    }
-  }
-  if constexpr (ACC) {
-    // one partial per lane for the tile this wave kept
-    const int vec = (rank % a.ntiles) * 8 + WT::v_of(lane);
-    const unsigned base = wt_base<N, 4, true>(WT::j_of(lane), vec, vec < a.nvec);
-    const Rsrc dp = make_rsrc(a.dphi_part + (size_t)(rank / a.ntiles) * nn, (unsigned)nn * 4u);
-    static_for<0, N1>(
-        [&](auto k) { bstore_f_so(dp, base, wt_soff<N, 4, true, k.value>(), acc_lds[k.value * 64 + lane]); });
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Row layer passes at N = 500 (25 x 20 Cooley-Tukey) on wave tiles.  The
-// 16-vector workgroup tiles this plan needs are five waves of 68 KB, which
-// run alone on their CU; here a workgroup is one wave of 17 KB and
-// transforms 3 whole rows.  Lane (r, j), r = lane / 20, j = lane mod 20,
-// holds A-item j of row r in registers (lanes 60..63 read row 0's items,
-// write nothing and touch no global memory).  The exchange runs through a
-// private buffer, slot s of row r at r * 525 + s + s / 20, so that the
-// elements of the A-items and the 20 B-items a wave reads at once start in
-// distinct bank pairs; B-items k1 < 20 go one per lane, the five left
-// (k1 = 20..24) one per lane quad, split by Good-Thomas 4 x 5 as in
-// b_spectral_quad.  Fields, this layer's modulation table and the dphi
-// partials are [vec][q] (rows, slot order): consecutive lanes read
-// consecutive slots of a row.  First pass (kPropOnce, real amplitudes in)
-// and forward (kFwdMid): one item per workgroup; adjoint (kBwdMid):
-// persistent, as fresnel_pass.
-// ---------------------------------------------------------------------------
-template <class PL>
-struct WideRows {
-  static constexpr int N = PL::N;
-  static constexpr int N1 = PL::N1;
-  static constexpr int N2 = PL::N2;
-  static constexpr int R = 64 / N2;      // rows per wave
-  static constexpr int P1 = N2 + 1;      // buffer stride of a B-item
-  static constexpr int PR = P1 * N1;     // buffer pitch of a row
-  static constexpr int Q = N2 / 4;       // the quad split's odd factor
-  static constexpr int E1 = Q * inv_mod(Q % 4, 4);
-  static constexpr int E2 = 4 * inv_mod(4 % Q, Q);
-  static_assert(N == 500 && N1 == 25 && N2 == 20 && !PL::PFA, "wide row tiles are written for 25 x 20");
-  static_assert(N1 - N2 == Q, "the last round is one item per quad");
-};
-
-template <class PL, int KIND>
-__global__ void __launch_bounds__(64, KIND == kBwdMid ? 2 : 3) wide_row_pass(PassArgs a) {
-  using W = WideRows<PL>;
-  constexpr int N = W::N;
-  constexpr int N1 = W::N1;
-  constexpr int N2 = W::N2;
-  constexpr int R = W::R;
-  constexpr int P1 = W::P1;
-  constexpr int PR = W::PR;
-  constexpr int Q = W::Q;
-  constexpr bool ACC = KIND == kBwdMid;
-  static_assert(KIND == kPropOnce || KIND == kFwdMid || KIND == kBwdMid, "wide row tiles run the layer kinds");
-  constexpr int POL = field_load_policy<N>();
-  // The adjoint stages the chirp in shared memory (B-item k1, frequency k2
-  // at P1 * k1 + k2; its registers allow 8 waves per CU either way); the
-  // forward kinds read it from the (cached) table in global memory, which
-  // leaves 12.6 KB of shared memory per wave: 12 waves per CU.
-  constexpr bool TAB_LDS = ACC;
-  __shared__ float2 tab[TAB_LDS ? PR : 1];
-  __shared__ float2 xch[R * PR];  // R rows
-
-  const int rank = (int)blockIdx.x;
-  if (rank >= a.workers) return;
-  const int lane = (int)threadIdx.x;
-  const bool act = lane < R * N2;
-  const int r = act ? lane / N2 : 0;
-  const int j = act ? lane - r * N2 : lane - R * N2;
-  const int total = a.ntiles * a.batch;
-  const size_t nn = (size_t)N * N;
-  const bool cj = a.conj_tab != 0;
-
-  if constexpr (TAB_LDS) {
-    for (int i = lane; i < N; i += 64) tab[P1 * (i / N2) + i % N2] = a.tab[PL::freq(i / N2, i % N2)];
-  }
-  // chirp entry of B-item k1, element k2 (frequency k1 + N1 * k2)
-  const float2* __restrict__ gtab = a.tab;
-  auto chirp = [&](int k1, int k2) -> float2 {
-    if constexpr (TAB_LDS) {
-      return tab[P1 * k1 + k2];
-    } else {
-      return gtab[k1 + N1 * k2];
-    }
-  };
-  float acc[ACC ? N1 : 1];
-  if constexpr (ACC) {
-    static_for<0, N1>([&](auto k) { acc[k.value] = 0.f; });
-  }
-
-  // one 1-D propagation of this lane's A-item along its row.  The lane's
-  // indices pass through an empty asm statement at every call, so the
-  // twiddles and addresses derived from them are formed here and not kept
-  // live across the item loop; scheduling barriers keep each phase's loads
-  // (data, twiddles, table) next to their use, as in b_spectral_item.
-  auto prop = [&](float2(&v)[N1], bool conj_t) {
-    int jo = j;
-    int ro = r;
-    asm volatile("" : "+v"(jo), "+v"(ro));
-    Dft<N1, -1>::run(v);
-    float2* const xr = xch + ro * PR;
-    if (act) {
-      static_for<0, N1>([&](auto x) { xr[P1 * x.value + jo] = v[x.value]; });
-    }
-    __syncthreads();
-    if (act) {
-      // B-item k1 = j of row r
-      float2* const yb = xr + P1 * jo;
-      float2 y[N2];
-      static_for<0, N2>([&](auto q) { y[q.value] = yb[q.value]; });
-      static_for<1, N2>([&](auto q) { y[q.value] = cmul(y[q.value], root_at<N>((unsigned)(jo * q.value))); });
-      Dft<N2, -1>::run(y);
-      __builtin_amdgcn_sched_barrier(0);
-      if (conj_t) {
-        static_for<0, N2>([&](auto q) { y[q.value] = cmulc(y[q.value], chirp(jo, q.value)); });
-      } else {
-        static_for<0, N2>([&](auto q) { y[q.value] = cmul(y[q.value], chirp(jo, q.value)); });
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      Dft<N2, 1>::run(y);
-      static_for<1, N2>(
-          [&](auto q) { y[q.value] = cmul(y[q.value], root_at<N>((unsigned)(N - jo * q.value))); });
-      static_for<0, N2>([&](auto q) { yb[q.value] = y[q.value]; });
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    if (lane < R * N2) {
-      // B-items k1 = N2 .. N1-1: item qi = lane / 4 (row qi / Q, k1 = N2 + qi mod Q), one per quad
-      // (the last quad, lanes 60..63, has none)
-      int t = lane;
-      asm volatile("" : "+v"(t));
-      const int qi = t >> 2;
-      const int qq = t & 3;
-      const int qrow = qi / Q;
-      const int k1 = N2 + qi - qrow * Q;
-      float2* const base = xch + qrow * PR + P1 * k1;
-      auto elem = [&](auto m) {
-        const int e = Q * qq + 4 * decltype(m)::value;
-        return e >= N2 ? e - N2 : e;
-      };
-      const float s1 = (qq & 1) ? -1.f : 1.f;
-      const float s2 = (qq & 2) ? -1.f : 1.f;
-      const bool l3 = qq == 3;
-      float2 z[Q];
-      static_for<0, Q>([&](auto m) {
-        const int e = elem(m);
-        z[m.value] = cmul(base[e], root_at<N>((unsigned)(k1 * e)));
-      });
-      Dft<Q, -1>::run(z);
-      quad_butterfly<2, Q>(z, s2);
-      static_for<0, Q>([&](auto m) {
-        const float2 u = z[m.value];
-        z[m.value] = l3 ? c2(u.y, -u.x) : u;
-      });
-      quad_butterfly<1, Q>(z, s1);
-      const int k4 = ((qq & 1) << 1) | (qq >> 1);
-      static_for<0, Q>([&](auto m) {
-        const int f = (W::E1 * k4 + W::E2 * decltype(m)::value) % N2;
-        const float2 h = chirp(k1, f);
-        z[m.value] = conj_t ? cmulc(z[m.value], h) : cmul(z[m.value], h);
-      });
-      quad_butterfly<1, Q>(z, s1);
-      static_for<0, Q>([&](auto m) {
-        const float2 u = z[m.value];
-        z[m.value] = l3 ? c2(-u.y, u.x) : u;
-      });
-      quad_butterfly<2, Q>(z, s2);
-      Dft<Q, 1>::run(z);
-      static_for<0, Q>([&](auto m) {
-        const int e = elem(m);
-        base[e] = cmul(z[m.value], root_at<N>((unsigned)(N - k1 * e)));
-      });
-    }
-    __syncthreads();
-    static_for<0, N1>([&](auto x) { v[x.value] = xr[P1 * x.value + jo]; });
-    Dft<N1, 1>::run(v);
-  };
-
-  // element x of this lane's A-item: [vec][q] offset vec * N + j + N2 * x
-  for (int it = rank; it < total; it += a.workers) {
-    const int tile = it % a.ntiles;
-    const int b = it / a.ntiles;
-    const int vec = tile * R + r;
-    const bool vok = act && vec < a.nvec;
-    const unsigned base = vok ? (unsigned)(vec * N + j) * 8u : kOutOfRange;
-    const Rsrc rin = make_rsrc(static_cast<const float2*>(a.in) + (size_t)b * nn, (unsigned)nn * 8u);
-    const Rsrc rmod = make_rsrc(a.mod, (unsigned)nn * 8u);
-    float2 x[N1];
-    if constexpr (ACC) {
-      // A_l from the saved input of the forward pass, then G's half hop
-      float2 ar[N1];
-      const Rsrc ract = make_rsrc(a.act_in + (size_t)b * nn, (unsigned)nn * 8u);
-      static_for<0, N1>([&](auto k) { ar[k.value] = bload_so<POL>(ract, base, N2 * 8 * k.value); });
-      prop(ar, false);
-      static_for<0, N1>([&](auto k) { x[k.value] = bload_so<POL>(rin, base, N2 * 8 * k.value); });
-      prop(x, true);
-      // conj(M_l) G_l and dphi_l += Im(conj(A_l) conj(M_l) G_l)
-      static_for<0, N1>([&](auto k) {
-        const float2 h = cmulc(x[k.value], bload_keep_so(rmod, base, N2 * 8 * k.value));
-        acc[k.value] += ar[k.value].x * h.y - ar[k.value].y * h.x;
-        x[k.value] = h;
-      });
-      prop(x, true);
-    } else if constexpr (KIND == kPropOnce) {
-      // real amplitudes in; along a row slot order is natural order (Cooley-Tukey plan)
-      const Rsrc ramp = make_rsrc(static_cast<const float*>(a.in) + (size_t)b * nn, (unsigned)nn * 4u);
-      const unsigned base4 = vok ? (unsigned)(vec * N + j) * 4u : kOutOfRange;
-      static_for<0, N1>([&](auto k) {
-        x[k.value] = c2(__builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ramp, (int)base4, N2 * 4 * k.value, POL)), 0.f);
-      });
-      prop(x, cj);
-    } else {
-      static_for<0, N1>([&](auto k) { x[k.value] = bload_so<POL>(rin, base, N2 * 8 * k.value); });
-      prop(x, cj);
-      // U_l = M_l A_l
-      static_for<0, N1>([&](auto k) { x[k.value] = cmul(x[k.value], bload_keep_so(rmod, base, N2 * 8 * k.value)); });
-      prop(x, cj);
-    }
+    load_field(rin, x);
+    float2 m[N1];
+    prop(x, a.conj_tab != 0, nothing);
+    load_mod(m);
+    static_for<0, N1>([&](auto k) { x[k.value] = cmul(x[k.value], m[k.value]); });
+    prop(x, a.conj_tab != 0, nothing);
     const Rsrc rout = make_rsrc(a.out + (size_t)b * nn, (unsigned)nn * 8u);
-    static_for<0, N1>([&](auto k) { bstore_so(rout, base, N2 * 8 * k.value, x[k.value]); });
-  }
-  if constexpr (ACC) {
-    // one partial per lane for the tile this wave kept
-    const int vec = (rank % a.ntiles) * R + r;
-    const bool vok = act && vec < a.nvec;
-    const unsigned base = vok ? (unsigned)(vec * N + j) * 4u : kOutOfRange;
-    const Rsrc dp = make_rsrc(a.dphi_part + (size_t)(rank / a.ntiles) * nn, (unsigned)nn * 4u);
-    static_for<0, N1>([&](auto k) { bstore_f_so(dp, base, N2 * 4 * k.value, acc[k.value]); });
+    static_for<0, N1>([&](auto k) { bstore_so(rout, fb, wt_soff<N, 8, FQ, k.value>(), x[k.value]); });
   }
 }
 
@@ -1944,113 +1670,8 @@ hipError_t launch_field_fwd_n(const FieldArgs& a, hipStream_t st) {
 }
 
 // ---------------------------------------------------------------------------
-// Per-size launchers (explicitly instantiated in one translation unit per size)
+// Residency
 // ---------------------------------------------------------------------------
-
-// Vectors per workgroup by FFT length (the workgroup has T * N2 threads).
-template <int N> struct TileT;
-template <> struct TileT<64>   { static constexpr int T = 16; };
-template <> struct TileT<100>  { static constexpr int T = 16; };
-template <> struct TileT<128>  { static constexpr int T = 16; };
-template <> struct TileT<200>  { static constexpr int T = 32; };  // detector-plane passes: 47.7 -> 45.7 and 30.6 -> 29.7 us against 16
-template <> struct TileT<256>  { static constexpr int T = 8; };
-template <> struct TileT<350>  { static constexpr int T = 32; };  // 14 slots: T * 14 threads must be whole waves
-template <> struct TileT<400>  { static constexpr int T = 8; };
-template <> struct TileT<500>  { static constexpr int T = 16; };  // 20 slots: T * 20 threads must be whole waves
-template <> struct TileT<512>  { static constexpr int T = 8; };
-template <> struct TileT<1000> { static constexpr int T = 8; };
-template <> struct TileT<1024> { static constexpr int T = 8; };
-
-template <int N>
-using CfgFor = Cfg<typename PlanFor<N>::type, TileT<N>::T>;
-template <int N>
-using RowCfgFor = Cfg<typename RowPlanFor<N>::type, TileT<N>::T>;
-
-// Vectors per workgroup of the separable layer passes, by kind and axis where
-// a measured sweep preferred another width than the size default (fields and
-// tables do not depend on it).
-template <int N, int KIND, int AXIS>
-struct LayerTile {
-  static constexpr int T = TileT<N>::T;
-};
-template <> struct LayerTile<200, kFwdMid, kCol> { static constexpr int T = 32; };
-template <> struct LayerTile<200, kPropOnce, kRow> { static constexpr int T = 32; };
-template <> struct LayerTile<200, kBwdMid, kCol> { static constexpr int T = 16; };
-template <> struct LayerTile<200, kFwdMid, kRow> { static constexpr int T = 8; };
-template <> struct LayerTile<200, kBwdMid, kRow> { static constexpr int T = 8; };
-template <> struct LayerTile<200, kBwdLast, kCol> { static constexpr int T = 32; };
-// 400: the column layer passes at 16 vectors (pitch 17: the A-item and
-// B-item reads of a 16-lane group fall in distinct bank pairs; at 8 vectors
-// two B-items share each group's pairs), four-wave workgroups of 55 KB, 8
-// waves per CU against 10; the row passes keep 8 (5-layer training step,
-// batch 500: adjoint column passes 576 -> 485 us and 391 -> 337 us; rows at 16
-// measured slower, 360 -> 380 us forward, and so did every pass at 512)
-template <> struct LayerTile<400, kFwdMid, kCol> { static constexpr int T = 16; };
-template <> struct LayerTile<400, kBwdMid, kCol> { static constexpr int T = 16; };
-template <> struct LayerTile<400, kBwdLast, kCol> { static constexpr int T = 16; };
-// 500: the forward passes in one ten-wave workgroup of 32 vectors per CU
-// instead of one five-wave workgroup of 16 (a 68 KB five-wave workgroup
-// leaves no room for a second one on a CU)
-template <> struct LayerTile<500, kPropOnce, kRow> { static constexpr int T = 32; };
-template <> struct LayerTile<500, kFwdMid, kRow> { static constexpr int T = 32; };
-template <> struct LayerTile<500, kFwdMid, kCol> { static constexpr int T = 32; };
-// 512: the first and the adjoint row passes at 16 vectors (5-layer training
-// step, batch 500: 446 -> 429 and 1113 -> 1077 us, step 11.22 -> 11.11 ms)
-template <> struct LayerTile<512, kPropOnce, kRow> { static constexpr int T = 16; };
-template <> struct LayerTile<512, kBwdMid, kRow> { static constexpr int T = 16; };
-template <> struct LayerTile<1000, kPropOnce, kRow> { static constexpr int T = 16; };
-template <> struct LayerTile<1000, kFwdMid, kRow> { static constexpr int T = 16; };
-template <> struct LayerTile<1000, kFwdMid, kCol> { static constexpr int T = 16; };
-// (its detector-plane passes measured slower at 16: 185 -> 215 us for the seed
-// pass of a 1000 x 1000 training step, batch 16)
-// (the adjoint passes keep 16: at 32 their registers, capped at 168 for ten
-// waves, spill, and the column pass measured slower; so do the detector-plane
-// passes, which transform only the covered rows and measured slower at 32)
-
-template <int N, int KIND, int AXIS>
-using LayerCfg = Cfg<std::conditional_t<AXIS == kRow, typename RowPlanFor<N>::type, typename PlanFor<N>::type>,
-                     LayerTile<N, KIND, AXIS>::T>;
-
-// Layer kinds of a slot-ordered field run as wave tiles where the plan allows,
-// along rows: there each wave's loads cover 8 whole 64-byte runs of its rows.
-// Along columns a wave covers half of each 128-byte line and the other half
-// is fetched again by the next tile (counters: 450 against 348 MB per
-// forward layer pass at N = 200), so columns keep the workgroup tiles.
-template <int N, int KIND, int AXIS>
-constexpr bool wave_tile_kind() {
-  using PL = typename PlanFor<N>::type;
-  return AXIS == kRow && PL::N2 == 8 && std::is_same_v<PL, typename RowPlanFor<N>::type> &&
-         (KIND == kFwdMid || KIND == kBwdMid || KIND == kBwdLast);
-}
-
-// Row layer kinds at 500 points run on the wide row tiles (wide_row_pass).
-template <int N, int KIND, int AXIS>
-constexpr bool wide_row_kind() {
-  return N == 500 && AXIS == kRow && (KIND == kPropOnce || KIND == kFwdMid || KIND == kBwdMid);
-}
-
-template <int N, int KIND, int AXIS, bool FULL>
-hipError_t launch_fr(const PassArgs& a, hipStream_t st) {
-  if constexpr (FULL && wide_row_kind<N, KIND, AXIS>()) {
-    if (a.workers < 1) return hipErrorInvalidValue;
-    const dim3 grid(8 * ((a.workers + 7) / 8));
-    hipLaunchKernelGGL((wide_row_pass<typename PlanFor<N>::type, KIND>), grid, dim3(64), 0, st, a);
-  } else if constexpr (FULL && wave_tile_kind<N, KIND, AXIS>()) {
-    if (a.workers < 1) return hipErrorInvalidValue;
-    const dim3 grid(8 * ((a.workers + 7) / 8));
-    hipLaunchKernelGGL((wave_pass<typename PlanFor<N>::type, KIND, AXIS>), grid, dim3(64), 0, st, a);
-  } else if constexpr (KIND == kFwdLast || KIND == kBwdFirst) {
-    using C = std::conditional_t<AXIS == kRow, RowCfgFor<N>, CfgFor<N>>;
-    const dim3 grid(work_grid(a.ntiles, (a.batch + a.spg - 1) / a.spg));
-    hipLaunchKernelGGL((detector_pass<C, KIND, AXIS, FULL>), grid, dim3(C::P), 0, st, a);
-  } else {
-    using C = LayerCfg<N, KIND, AXIS>;
-    if (a.workers < 1) return hipErrorInvalidValue;
-    const dim3 grid(8 * ((a.workers + 7) / 8));
-    hipLaunchKernelGGL((fresnel_pass<C, KIND, AXIS, FULL>), grid, dim3(C::P), 0, st, a);
-  }
-  return hipGetLastError();
-}
 
 // Compute units of the current device (cached per device).
 inline int device_cus() {
@@ -2082,92 +1703,6 @@ inline int resident_per_cu(const void* kernel, int block) {
   const size_t lds = (at.sharedSizeBytes + granule - 1) / granule * granule;
   if (lds > 0) nb = std::min(nb, static_cast<int>(static_cast<size_t>(lds_cu) / lds));
   return nb;
-}
-
-template <int N, int KIND, int AXIS, bool FULL>
-int slots_fr() {
-  static int per_cu = 0;
-  if (per_cu == 0) {
-    if constexpr (FULL && wide_row_kind<N, KIND, AXIS>()) {
-      per_cu = resident_per_cu(reinterpret_cast<const void*>(&wide_row_pass<typename PlanFor<N>::type, KIND>), 64);
-    } else if constexpr (FULL && wave_tile_kind<N, KIND, AXIS>()) {
-      per_cu = resident_per_cu(reinterpret_cast<const void*>(&wave_pass<typename PlanFor<N>::type, KIND, AXIS>), 64);
-    } else {
-      using C = LayerCfg<N, KIND, AXIS>;
-      per_cu = resident_per_cu(reinterpret_cast<const void*>(&fresnel_pass<C, KIND, AXIS, FULL>), C::P);
-    }
-  }
-  return per_cu * device_cus();
-}
-
-template <int N, int KIND>
-int slots_fr_axis(Axis axis, bool full) {
-  if (full) return axis == kRow ? slots_fr<N, KIND, kRow, true>() : slots_fr<N, KIND, kCol, true>();
-  return axis == kRow ? slots_fr<N, KIND, kRow, false>() : slots_fr<N, KIND, kCol, false>();
-}
-
-template <int N, int KIND>
-int tile_fr_axis(Axis axis, bool full) {
-  if constexpr (wide_row_kind<N, KIND, kRow>()) {
-    if (axis == kRow && full) return WideRows<typename PlanFor<N>::type>::R;
-  }
-  if (axis == kRow) return full && wave_tile_kind<N, KIND, kRow>() ? 8 : LayerTile<N, KIND, kRow>::T;
-  return full && wave_tile_kind<N, KIND, kCol>() ? 8 : LayerTile<N, KIND, kCol>::T;
-}
-
-// Vectors per workgroup of a separable pass.
-template <int N>
-int tile_fr_n(PassKind kind, Axis axis, bool full) {
-  switch (kind) {
-    case kPropOnce: return tile_fr_axis<N, kPropOnce>(axis, full);
-    case kFwdMid: return tile_fr_axis<N, kFwdMid>(axis, full);
-    case kBwdMid: return tile_fr_axis<N, kBwdMid>(axis, full);
-    case kBwdLast: return tile_fr_axis<N, kBwdLast>(axis, full);
-    default: return TileT<N>::T;  // detector-plane passes
-  }
-}
-
-template <int N>
-int slots_fr_n(PassKind kind, Axis axis, bool full) {
-  switch (kind) {
-    case kPropOnce: return slots_fr_axis<N, kPropOnce>(axis, full);
-    case kFwdMid: return slots_fr_axis<N, kFwdMid>(axis, full);
-    case kBwdMid: return slots_fr_axis<N, kBwdMid>(axis, full);
-    case kBwdLast: return slots_fr_axis<N, kBwdLast>(axis, full);
-    default: return 0;
-  }
-}
-
-template <int N, int KIND>
-hipError_t launch_fr_axis(Axis axis, const PassArgs& a, hipStream_t st) {
-  if (a.full) return axis == kRow ? launch_fr<N, KIND, kRow, true>(a, st) : launch_fr<N, KIND, kCol, true>(a, st);
-  return axis == kRow ? launch_fr<N, KIND, kRow, false>(a, st) : launch_fr<N, KIND, kCol, false>(a, st);
-}
-
-template <int N>
-hipError_t launch_fr_n(PassKind kind, Axis axis, const PassArgs& a, hipStream_t st) {
-  if (a.full && a.n != N) return hipErrorInvalidValue;
-  switch (kind) {
-    case kPropOnce: return launch_fr_axis<N, kPropOnce>(axis, a, st);
-    case kFwdMid: return launch_fr_axis<N, kFwdMid>(axis, a, st);
-    case kFwdLast: return launch_fr_axis<N, kFwdLast>(axis, a, st);
-    case kBwdFirst: return launch_fr_axis<N, kBwdFirst>(axis, a, st);
-    case kBwdMid: return launch_fr_axis<N, kBwdMid>(axis, a, st);
-    case kBwdLast: return launch_fr_axis<N, kBwdLast>(axis, a, st);
-  }
-  return hipErrorInvalidValue;
-}
-
-template <int N>
-TileShape shape_n() { return TileShape{CfgFor<N>::T, CfgFor<N>::S}; }
-
-// The slot order of the separable passes' stored fields: rows and columns
-// use the same plan, so one map serves both axes.
-template <int N>
-SlotMap slot_map_n() {
-  using PL = typename PlanFor<N>::type;
-  static_assert(std::is_same_v<PL, typename RowPlanFor<N>::type>, "stored slot order needs one plan for both axes");
-  return SlotMap{PL::N1, PL::N2, PL::PFA ? 1 : 0};
 }
 
 }  // namespace lr
