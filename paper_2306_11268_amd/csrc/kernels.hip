@@ -111,140 +111,187 @@ __global__ void __launch_bounds__(1024) loss_kernel(int kind, const float* __res
   if (threadIdx.x == 0 && loss) *loss = tot * invb;
 }
 
-// One Adam step on every element: m = b1 m + (1-b1) g, v = b2 v + (1-b2) g^2,
-// phi -= lr * (m / bc1) / (sqrt(v / bc2) + eps), bc = 1 - beta^t.
 // Codesign layer (§3.2): per pixel, w = softmax((logits + noise) / tau) over
 // the K device levels; the phase is sum_k w_k levels_k, or (hard) the level
-// of the largest logits + noise, the first on ties.  One wave per pixel; lane
-// l handles levels l, l + 64, ...; the scores are read coalesced.
+// of the largest logits + noise, the first on ties.  The gradient (the soft
+// Jacobian, also the straight-through gradient of the hard layer) is
+// dL/dlogit_j = w_j (levels_j - sum_k w_k levels_k) dL/dphi / tau.
+//
+// A streaming pass over the scores: G = 1 .. 64 lanes hold a pixel's scores in
+// registers (as many as K needs, so that a wave carries 64 / G pixels), read
+// once in 16-byte pieces where K and the pointers allow, U pixels in flight per
+// lane group, every exponential formed once.  One wave per pixel reading
+// 4-byte values, one pixel at a time, was held by the latency of its loads and
+// its chain of reductions: 200 000 pixels of 256 levels 134 -> 68 us forward
+// (410 MB, 6.1 TB/s) and 168 -> 108 us backward (615 MB, 5.7 TB/s), 300 000
+// of 64 levels 76 -> 25 and 72 -> 36.
 constexpr int kCodesignMaxLevels = 1024;
 
-__device__ __forceinline__ float wave_max(float x) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) x = fmaxf(x, __shfl_xor(x, o, 64));
-  return x;
+// Lane i's partner within groups of 2, 4, 8 and 16 lanes: any lane of the other
+// half of the group, all of whose lanes hold the same partial result.
+template <int CTRL>
+__device__ __forceinline__ float dpp_move(float x) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xF, 0xF, false));
 }
-__device__ __forceinline__ int wave_min_int(int x) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) x = min(x, __shfl_xor(x, o, 64));
+template <int G, class Op>
+__device__ __forceinline__ float group_reduce(float x, Op op) {
+  if constexpr (G >= 2) x = op(x, dpp_move<0xB1>(x));    // quad_perm [1,0,3,2]
+  if constexpr (G >= 4) x = op(x, dpp_move<0x4E>(x));    // quad_perm [2,3,0,1]
+  if constexpr (G >= 8) x = op(x, dpp_move<0x141>(x));   // row_half_mirror
+  if constexpr (G >= 16) x = op(x, dpp_move<0x140>(x));  // row_mirror
+  if constexpr (G >= 32) x = op(x, __shfl_xor(x, 16, 64));
+  if constexpr (G >= 64) x = op(x, __shfl_xor(x, 32, 64));
   return x;
 }
 
-// Per-pixel softmax statistics: max of y = (logits + noise) / tau, the first
-// level index reaching the largest logits + noise, and sum_k exp(y_k - max).
-// The scores of a pixel are read once into registers: lane l holds
-// s[i] = logits + noise of level l + 64 i, i < NI = ceil(K / 64) (-inf past K).
-struct CodesignStats {
-  float ymax;
-  int kbest;
-  float esum;
+// VEC: value i of the lane's NV float4 (i = 4 * v + c) is level 4 * (lane + G * v)
+// + c; else value i is level lane + G * i.
+template <int G, int NV, bool VEC>
+struct CodesignShape {
+  static constexpr int N = VEC ? 4 * NV : NV;
+  static __device__ __forceinline__ int level(int lane, int i) {
+    return VEC ? 4 * (lane + G * (i / 4)) + i % 4 : lane + G * i;
+  }
 };
-template <int NI>
-__device__ __forceinline__ void codesign_load(const float* __restrict__ lg, const float* __restrict__ nz, int K,
-                                              int lane, float (&sc)[NI]) {
+
+template <int G, int NV, bool VEC>
+__device__ __forceinline__ void codesign_read(const float* __restrict__ p, int K, int lane, bool ok,
+                                              float (&v)[CodesignShape<G, NV, VEC>::N]) {
+  using S = CodesignShape<G, NV, VEC>;
+  if constexpr (VEC) {
 #pragma unroll
-  for (int i = 0; i < NI; ++i) {
-    const int k = lane + 64 * i;
-    sc[i] = k < K ? lg[k] + nz[k] : -INFINITY;
+    for (int i = 0; i < NV; ++i) {
+      const bool in = ok && S::level(lane, 4 * i) < K;
+      const float4 f = in ? *reinterpret_cast<const float4*>(p + S::level(lane, 4 * i)) : make_float4(0.f, 0.f, 0.f, 0.f);
+      v[4 * i] = f.x;
+      v[4 * i + 1] = f.y;
+      v[4 * i + 2] = f.z;
+      v[4 * i + 3] = f.w;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < NV; ++i) v[i] = ok && S::level(lane, i) < K ? p[S::level(lane, i)] : 0.f;
   }
-}
-template <int NI>
-__device__ __forceinline__ CodesignStats codesign_stats(const float (&sc)[NI], int K, float inv_tau, int lane) {
-  float smax = -INFINITY;
-#pragma unroll
-  for (int i = 0; i < NI; ++i) smax = fmaxf(smax, sc[i]);
-  smax = wave_max(smax);
-  int kb = K;
-#pragma unroll
-  for (int i = NI - 1; i >= 0; --i) {
-    const int k = lane + 64 * i;
-    if (k < K && sc[i] == smax) kb = k;  // the lowest level of this lane reaching the maximum
-  }
-  kb = wave_min_int(kb);
-  const float ymax = smax * inv_tau;
-  float es = 0.f;
-#pragma unroll
-  for (int i = 0; i < NI; ++i)
-    if (lane + 64 * i < K) es += expf(sc[i] * inv_tau - ymax);
-  return CodesignStats{ymax, kb, wave_sum(es)};
 }
 
-template <int NI>
+// BWD: out [count][K] = dL/dlogits; else out [count] = phases.
+template <int G, int NV, bool VEC, int U, bool BWD>
 __global__ void __launch_bounds__(256) codesign_kernel(const float* __restrict__ logits, const float* __restrict__ noise,
                                                        const float* __restrict__ levels, int K, long long count,
-                                                       float inv_tau, int hard, float* __restrict__ phi) {
-  const int lane = threadIdx.x & 63;
-  const long long waves = (long long)gridDim.x * (blockDim.x >> 6);
-  for (long long p = (long long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); p < count; p += waves) {
-    float sc[NI];
-    codesign_load<NI>(logits + p * K, noise + p * K, K, lane, sc);
-    const CodesignStats cs = codesign_stats<NI>(sc, K, inv_tau, lane);
-    float out;
-    if (hard) {
-      out = levels[cs.kbest < K ? cs.kbest : 0];  // (no index reaches the maximum only for NaN scores)
-    } else {
-      float acc = 0.f;
+                                                       float inv_tau, int hard, const float* __restrict__ grad_phi,
+                                                       float* __restrict__ out) {
+  using S = CodesignShape<G, NV, VEC>;
+  constexpr int N = S::N;
+  constexpr int PER = 256 / G;  // lane groups per workgroup
+  const int lane = threadIdx.x % G;
+  const int group = threadIdx.x / G;
+  auto fmax2 = [](float a, float b) { return fmaxf(a, b); };
+  auto fsum2 = [](float a, float b) { return a + b; };
+  float lv[N];
+  codesign_read<G, NV, VEC>(levels, K, lane, true, lv);
+  const long long step = (long long)gridDim.x * PER * U;
+  for (long long p0 = ((long long)blockIdx.x * U) * PER + group; p0 < count + group; p0 += step) {
+    float sc[U][N];
+    float nz[U][N];
 #pragma unroll
-      for (int i = 0; i < NI; ++i) {
-        const int k = lane + 64 * i;
-        if (k < K) acc += expf(sc[i] * inv_tau - cs.ymax) * levels[k];
-      }
-      out = wave_sum(acc) / cs.esum;
+    for (int u = 0; u < U; ++u) {
+      const long long p = p0 + (long long)u * PER;
+      codesign_read<G, NV, VEC>(logits + p * K, K, lane, p < count, sc[u]);
+      codesign_read<G, NV, VEC>(noise + p * K, K, lane, p < count, nz[u]);
     }
-    if (lane == 0) phi[p] = out;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const long long p = p0 + (long long)u * PER;
+      float smax = -INFINITY;
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        sc[u][i] = S::level(lane, i) < K ? sc[u][i] + nz[u][i] : -INFINITY;
+        smax = fmaxf(smax, sc[u][i]);
+      }
+      smax = group_reduce<G>(smax, fmax2);
+      if (!BWD && hard) {
+        // the first level reaching the maximum, and its phase
+        int kb = K;
+#pragma unroll
+        for (int i = N - 1; i >= 0; --i) {
+          const int k = S::level(lane, i);
+          if (k < K && sc[u][i] == smax) kb = k;
+        }
+        // (level indices are exact in float32)
+        const float kf = group_reduce<G>((float)kb, [](float a, float b) { return fminf(a, b); });
+        const int k = (int)kf;
+        if (lane == 0 && p < count) out[p] = levels[k < K ? k : 0];  // (none reaches it only for NaN scores)
+        continue;
+      }
+      float es = 0.f;
+      float ws = 0.f;
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        const float e = S::level(lane, i) < K ? expf((sc[u][i] - smax) * inv_tau) : 0.f;
+        es += e;
+        ws += e * lv[i];
+        sc[u][i] = e;
+      }
+      es = group_reduce<G>(es, fsum2);
+      ws = group_reduce<G>(ws, fsum2);
+      if constexpr (!BWD) {
+        if (lane == 0 && p < count) out[p] = ws / es;
+      } else {
+        const float inv_s = 1.f / es;
+        const float mean = ws * inv_s;
+        const float gs = p < count ? grad_phi[p] * inv_tau : 0.f;
+#pragma unroll
+        for (int i = 0; i < N; ++i) sc[u][i] = sc[u][i] * inv_s * (lv[i] - mean) * gs;
+        if (p < count) {
+          float* o = out + p * K;
+          if constexpr (VEC) {
+#pragma unroll
+            for (int i = 0; i < NV; ++i) {
+              const int k = S::level(lane, 4 * i);
+              if (k < K)
+                *reinterpret_cast<float4*>(o + k) =
+                    make_float4(sc[u][4 * i], sc[u][4 * i + 1], sc[u][4 * i + 2], sc[u][4 * i + 3]);
+            }
+          } else {
+#pragma unroll
+            for (int i = 0; i < NV; ++i)
+              if (S::level(lane, i) < K) o[S::level(lane, i)] = sc[u][i];
+          }
+        }
+      }
+    }
   }
 }
 
-// dL/dlogit_j = w_j (levels_j - sum_k w_k levels_k) dL/dphi / tau (the soft
-// Jacobian, also the straight-through gradient of the hard layer).
-template <int NI>
-__global__ void __launch_bounds__(256) codesign_bwd_kernel(const float* __restrict__ logits,
-                                                           const float* __restrict__ noise,
-                                                           const float* __restrict__ levels, int K, long long count,
-                                                           float inv_tau, const float* __restrict__ grad_phi,
-                                                           float* __restrict__ grad_logits) {
-  const int lane = threadIdx.x & 63;
-  const long long waves = (long long)gridDim.x * (blockDim.x >> 6);
-  for (long long p = (long long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); p < count; p += waves) {
-    float sc[NI];
-    codesign_load<NI>(logits + p * K, noise + p * K, K, lane, sc);
-    const CodesignStats cs = codesign_stats<NI>(sc, K, inv_tau, lane);
-    const float inv_s = 1.f / cs.esum;
-    float acc = 0.f;
-    float lv[NI];
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const int k = lane + 64 * i;
-      lv[i] = k < K ? levels[k] : 0.f;
-      if (k < K) acc += expf(sc[i] * inv_tau - cs.ymax) * lv[i];
-    }
-    const float mean = wave_sum(acc) * inv_s;
-    const float gs = grad_phi[p] * inv_tau;
-    float* gl = grad_logits + p * K;
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const int k = lane + 64 * i;
-      if (k < K) {
-        const float w = expf(sc[i] * inv_tau - cs.ymax) * inv_s;
-        gl[k] = w * (lv[i] - mean) * gs;
-      }
-    }
-  }
-}
-
-template <int NI>
-static void launch_codesign_ni(const float* logits, const float* noise, const float* levels, int K, long long count,
-                               float tau, int hard, const float* grad_phi, float* phi_or_grad, unsigned blocks,
-                               hipStream_t st) {
-  if (grad_phi) {
-    hipLaunchKernelGGL(codesign_bwd_kernel<NI>, dim3(blocks), dim3(256), 0, st, logits, noise, levels, K, count,
-                       1.f / tau, grad_phi, phi_or_grad);
+struct CodesignArgs {
+  const float* logits;
+  const float* noise;
+  const float* levels;
+  int K;
+  long long count;
+  float inv_tau;
+  int hard;
+  const float* grad_phi;
+  float* out;
+  hipStream_t st;
+};
+template <int G, int NV, bool VEC, int U>
+static void launch_codesign_shape(const CodesignArgs& a) {
+  constexpr int PER = 256 / G * U;  // pixels per workgroup and round
+  long long blocks = (a.count + PER - 1) / PER;
+  if (blocks > 65536) blocks = 65536;
+  const dim3 grid((unsigned)blocks);
+  if (a.grad_phi) {
+    hipLaunchKernelGGL((codesign_kernel<G, NV, VEC, U, true>), grid, dim3(256), 0, a.st, a.logits, a.noise, a.levels, a.K,
+                       a.count, a.inv_tau, a.hard, a.grad_phi, a.out);
   } else {
-    hipLaunchKernelGGL(codesign_kernel<NI>, dim3(blocks), dim3(256), 0, st, logits, noise, levels, K, count, 1.f / tau,
-                       hard, phi_or_grad);
+    hipLaunchKernelGGL((codesign_kernel<G, NV, VEC, U, false>), grid, dim3(256), 0, a.st, a.logits, a.noise, a.levels,
+                       a.K, a.count, a.inv_tau, a.hard, a.grad_phi, a.out);
   }
 }
 
+// One Adam step on every element: m = b1 m + (1-b1) g, v = b2 v + (1-b2) g^2,
+// phi -= lr * (m / bc1) / (sqrt(v / bc2) + eps), bc = 1 - beta^t.
 __global__ void adam_kernel(float* __restrict__ phi, const float* __restrict__ g, float* __restrict__ m,
                             float* __restrict__ v, long long count, float lr, float b1, float b2, float eps,
                             float bc1, float bc2) {
@@ -613,10 +660,50 @@ int as_pass_slots(int N, AsPassKind kind, bool half) {
 // Layer normalisation of intensity maps (per sample, over count values).
 // Chunk c of sample b covers values [c * kLnChunk, min(count, (c+1) * kLnChunk)).
 // ---------------------------------------------------------------------------
+// The chunk sits in registers between the two sums (16 values a thread), in
+// 16-byte pieces where the maps allow (VEC); the chunks are merged by one wave
+// in a fixed order, inside the last kernel for maps of up to kLnFuse chunks.
+// (64 maps of 350 x 350: 32 -> 16 us forward, 32 -> 26 us backward; 16 of 1000 x
+// 1000: 104 -> 35 and 106 -> 49; before,
+// every value was read twice by the first kernel, a thread per sample walked
+// its chunks and the last kernel divided 64-bit indices per value.)
 constexpr int kLnThreads = 256;
+constexpr int kLnPer = kLnChunk / kLnThreads;  // values per thread of a chunk
+constexpr int kLnFuse = 256;
+
+// f(i, offset, valid) for this thread's values of chunk c (offset inside the
+// sample); VEC: runs of four consecutive values.
+template <bool VEC, class F>
+__device__ __forceinline__ void ln_values(int c, long long count, F&& f) {
+  const long long lo = (long long)c * kLnChunk;
+#pragma unroll
+  for (int i = 0; i < kLnPer; ++i) {
+    const long long o = VEC ? lo + 4 * ((i / 4) * kLnThreads + (int)threadIdx.x) + i % 4
+                            : lo + i * kLnThreads + (int)threadIdx.x;
+    f(i, o, o < count);
+  }
+}
+template <bool VEC>
+__device__ __forceinline__ void ln_read(const float* __restrict__ x, int c, long long count, float (&v)[kLnPer]) {
+  if constexpr (VEC) {
+    const long long lo = (long long)c * kLnChunk;
+#pragma unroll
+    for (int i = 0; i < kLnPer / 4; ++i) {
+      const long long o = lo + 4 * (i * kLnThreads + (int)threadIdx.x);
+      const float4 q = o < count ? *reinterpret_cast<const float4*>(x + o) : make_float4(0.f, 0.f, 0.f, 0.f);
+      v[4 * i] = q.x;
+      v[4 * i + 1] = q.y;
+      v[4 * i + 2] = q.z;
+      v[4 * i + 3] = q.w;
+    }
+  } else {
+    ln_values<VEC>(c, count, [&](int i, long long o, bool ok) { v[i] = ok ? x[o] : 0.f; });
+  }
+}
 
 // g == nullptr: part = (chunk mean, sum of squared deviations from it);
 // otherwise part = (sum of g, sum of g * y) with y = x the normalised map.
+template <bool VEC>
 __global__ void __launch_bounds__(kLnThreads) ln_partial_kernel(const float* __restrict__ x,
                                                                 const float* __restrict__ g, long long count,
                                                                 int nchunks, float2* __restrict__ part) {
@@ -624,24 +711,29 @@ __global__ void __launch_bounds__(kLnThreads) ln_partial_kernel(const float* __r
   const int c = blockIdx.x;
   const int b = blockIdx.y;
   const size_t base = (size_t)b * (size_t)count;
-  const long long lo = (long long)c * kLnChunk;
-  const long long hi = min(count, lo + kLnChunk);
+  float v[kLnPer];
+  ln_read<VEC>(x + base, c, count, v);
   float s1 = 0.f;
   float s2 = 0.f;
   if (g == nullptr) {
-    for (long long i = lo + threadIdx.x; i < hi; i += kLnThreads) s1 += x[base + i];
-    const float mean = block_sum<kLnThreads>(s1, red) / (float)(hi - lo);
-    for (long long i = lo + threadIdx.x; i < hi; i += kLnThreads) {
-      const float d = x[base + i] - mean;
+    const long long left = count - (long long)c * kLnChunk;
+    const float n = (float)(left < kLnChunk ? left : kLnChunk);
+#pragma unroll
+    for (int i = 0; i < kLnPer; ++i) s1 += v[i];
+    const float mean = block_sum<kLnThreads>(s1, red) / n;
+    ln_values<VEC>(c, count, [&](int i, long long, bool ok) {
+      const float d = ok ? v[i] - mean : 0.f;
       s2 += d * d;
-    }
+    });
     const float m2 = block_sum<kLnThreads>(s2, red);
     if (threadIdx.x == 0) part[(size_t)b * nchunks + c] = c2(mean, m2);
   } else {
-    for (long long i = lo + threadIdx.x; i < hi; i += kLnThreads) {
-      const float gv = g[base + i];
-      s1 += gv;
-      s2 += gv * x[base + i];
+    float gv[kLnPer];
+    ln_read<VEC>(g + base, c, count, gv);
+#pragma unroll
+    for (int i = 0; i < kLnPer; ++i) {
+      s1 += gv[i];
+      s2 += gv[i] * v[i];
     }
     const float a = block_sum<kLnThreads>(s1, red);
     const float bsum = block_sum<kLnThreads>(s2, red);
@@ -649,87 +741,146 @@ __global__ void __launch_bounds__(kLnThreads) ln_partial_kernel(const float* __r
   }
 }
 
-// One thread per sample combines its chunks in order.  Forward: the chunk
-// means and squared-deviation sums merge by the pairwise update of Chan et
-// al.; stats = (mean, 1/sqrt(M2 / count + eps)).  Backward: stats2 =
-// (mean of g, mean of g * y).
-__global__ void ln_combine_kernel(const float2* __restrict__ part, int batch, long long count, int nchunks,
-                                  float eps, int backward, float2* __restrict__ out) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= batch) return;
-  const float2* p = part + (size_t)b * nchunks;
+// One wave merges the chunks of a sample: lane l takes chunks l, l + 64, ... in
+// order, then the lanes merge in a fixed butterfly.  Forward: chunk means and
+// squared-deviation sums by the pairwise update of Chan et al., returning
+// (mean, 1/sqrt(M2 / count + eps)); backward: (mean of g, mean of g * y).
+__device__ __forceinline__ float2 ln_merge(const float2* __restrict__ p, long long count, int nchunks, float eps,
+                                           bool backward) {
+  const int lane = threadIdx.x & 63;
   if (backward) {
     float a = 0.f;
     float m = 0.f;
-    for (int c = 0; c < nchunks; ++c) {
+    for (int c = lane; c < nchunks; c += 64) {
       a += p[c].x;
       m += p[c].y;
     }
-    out[b] = c2(a / (float)count, m / (float)count);
-    return;
+    return c2(wave_sum(a) / (float)count, wave_sum(m) / (float)count);
   }
   float n_a = 0.f;
   float mean = 0.f;
   float m2 = 0.f;
-  for (int c = 0; c < nchunks; ++c) {
-    const long long lo = (long long)c * kLnChunk;
-    const float n_b = (float)(min(count, lo + kLnChunk) - lo);
+  // (an empty side leaves the other as it is)
+  auto merge = [&](float n_b, float mean_b, float m2_b) {
     const float n = n_a + n_b;
-    const float delta = p[c].x - mean;
-    mean += delta * (n_b / n);
-    m2 += p[c].y + delta * delta * (n_a * n_b / n);
+    const float w = n > 0.f ? n_b / n : 0.f;
+    const float delta = mean_b - mean;
+    mean = n_a > 0.f ? mean + delta * w : mean_b;
+    m2 = m2 + m2_b + (n_a > 0.f && n_b > 0.f ? delta * delta * (n_a * w) : 0.f);
     n_a = n;
+  };
+  for (int c = lane; c < nchunks; c += 64) {
+    const long long left = count - (long long)c * kLnChunk;
+    merge((float)(left < kLnChunk ? left : kLnChunk), p[c].x, p[c].y);
   }
-  out[b] = c2(mean, 1.f / sqrtf(m2 / (float)count + eps));
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const float nb = __shfl_xor(n_a, o, 64);
+    const float mb = __shfl_xor(mean, o, 64);
+    const float qb = __shfl_xor(m2, o, 64);
+    if (nb > 0.f) merge(nb, mb, qb);
+  }
+  // every lane merged the same chunks, in its own order: lane 0's result
+  mean = __shfl(mean, 0, 64);
+  m2 = __shfl(m2, 0, 64);
+  return c2(mean, 1.f / sqrtf(m2 / (float)count + eps));
+}
+
+__global__ void __launch_bounds__(64) ln_combine_kernel(const float2* __restrict__ part, long long count, int nchunks,
+                                                        float eps, int backward, float2* __restrict__ out) {
+  const int b = blockIdx.x;
+  const float2 r = ln_merge(part + (size_t)b * nchunks, count, nchunks, eps, backward != 0);
+  if (threadIdx.x == 0) out[b] = r;
 }
 
 // Forward: y = (x - mean) * rstd.  Backward (g != nullptr, x = y the
-// normalised map): dx = rstd * (g - mean(g) - y * mean(g * y)).
-__global__ void ln_apply_kernel(const float* __restrict__ x, const float* __restrict__ g,
-                                const float2* __restrict__ stats, const float2* __restrict__ stats2, int batch,
-                                long long count, float* __restrict__ out) {
-  const size_t total = (size_t)batch * (size_t)count;
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
-    const size_t b = i / (size_t)count;
-    const float2 s = stats[b];
-    if (g == nullptr) {
-      out[i] = (x[i] - s.x) * s.y;
-    } else {
-      const float2 s2 = stats2[b];
-      out[i] = s.y * (g[i] - s2.x - x[i] * s2.y);
+// normalised map): dx = rstd * (g - mean(g) - y * mean(g * y)).  A workgroup
+// per chunk and sample; FUSE: it merges the sample's partials itself (part),
+// and chunk 0's writes them to the statistics.
+template <bool VEC, bool FUSE>
+__global__ void __launch_bounds__(kLnThreads) ln_apply_kernel(const float* __restrict__ x, const float* __restrict__ g,
+                                                              const float2* __restrict__ part, float2* stats,
+                                                              const float2* __restrict__ stats2, long long count,
+                                                              int nchunks, float eps, float* __restrict__ out) {
+  __shared__ float2 merged;
+  const int c = blockIdx.x;
+  const int b = blockIdx.y;
+  const size_t base = (size_t)b * (size_t)count;
+  float v[kLnPer];
+  float gv[kLnPer];
+  ln_read<VEC>(x + base, c, count, v);
+  if (g) ln_read<VEC>(g + base, c, count, gv);
+  float2 s;
+  float2 s2;
+  if constexpr (FUSE) {
+    if (threadIdx.x < 64) {
+      const float2 r = ln_merge(part + (size_t)b * nchunks, count, nchunks, eps, g != nullptr);
+      if (threadIdx.x == 0) {
+        merged = r;
+        if (!g && c == 0) stats[b] = r;
+      }
     }
+    __syncthreads();
+    s = g ? stats[b] : merged;
+    s2 = merged;
+  } else {
+    s = stats[b];
+    s2 = g ? stats2[b] : c2(0.f, 0.f);
+  }
+#pragma unroll
+  for (int i = 0; i < kLnPer; ++i) v[i] = g ? s.y * (gv[i] - s2.x - v[i] * s2.y) : (v[i] - s.x) * s.y;
+  if constexpr (VEC) {
+    const long long lo = (long long)c * kLnChunk;
+#pragma unroll
+    for (int i = 0; i < kLnPer / 4; ++i) {
+      const long long o = lo + 4 * (i * kLnThreads + (int)threadIdx.x);
+      if (o < count) *reinterpret_cast<float4*>(out + base + o) = make_float4(v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]);
+    }
+  } else {
+    ln_values<VEC>(c, count, [&](int i, long long o, bool ok) {
+      if (ok) out[base + o] = v[i];
+    });
   }
 }
 
-static int ln_apply_blocks(size_t total) {
-  size_t blocks = (total + 255) / 256;
-  if (blocks > 4096) blocks = 4096;
-  return blocks < 1 ? 1 : (int)blocks;
+// The three kernels of either direction (g null: forward).  The in-place forms
+// (out = x, or out = g) read a chunk whole before they write it.
+template <bool VEC>
+static hipError_t launch_ln(const float* x, const float* g, int batch, long long count, float eps, float* out,
+                            float2* stats, float2* part, float2* stats2, hipStream_t st) {
+  const int nchunks = (int)ln_chunks(count);
+  const dim3 grid(nchunks, batch);
+  hipLaunchKernelGGL(ln_partial_kernel<VEC>, grid, dim3(kLnThreads), 0, st, x, g, count, nchunks, part);
+  if (nchunks <= kLnFuse) {
+    hipLaunchKernelGGL((ln_apply_kernel<VEC, true>), grid, dim3(kLnThreads), 0, st, x, g, part, stats, stats2, count,
+                       nchunks, eps, out);
+  } else {
+    hipLaunchKernelGGL(ln_combine_kernel, dim3(batch), dim3(64), 0, st, part, count, nchunks, eps, g ? 1 : 0,
+                       g ? stats2 : stats);
+    hipLaunchKernelGGL((ln_apply_kernel<VEC, false>), grid, dim3(kLnThreads), 0, st, x, g, part, stats, stats2, count,
+                       nchunks, eps, out);
+  }
+  return hipGetLastError();
+}
+// Every map starts on 16 bytes and is a whole number of float4.
+static bool ln_vec(const void* a, const void* b, const void* c, long long count) {
+  auto ok = [](const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; };
+  return count % 4 == 0 && ok(a) && ok(b) && ok(c);
 }
 
 hipError_t launch_layer_norm(const float* x, int batch, long long count, float eps, float* y, float2* stats,
                              float2* part, hipStream_t st) {
   if (batch < 1 || batch > 65535 || count < 1 || ln_chunks(count) > (1 << 30)) return hipErrorInvalidValue;
-  const int nchunks = (int)ln_chunks(count);
-  hipLaunchKernelGGL(ln_partial_kernel, dim3(nchunks, batch), dim3(kLnThreads), 0, st, x, nullptr, count, nchunks,
-                     part);
-  hipLaunchKernelGGL(ln_combine_kernel, dim3((batch + 63) / 64), dim3(64), 0, st, part, batch, count, nchunks, eps, 0,
-                     stats);
-  hipLaunchKernelGGL(ln_apply_kernel, dim3(ln_apply_blocks((size_t)batch * count)), dim3(256), 0, st, x, nullptr,
-                     stats, nullptr, batch, count, y);
-  return hipGetLastError();
+  return ln_vec(x, y, nullptr, count) ? launch_ln<true>(x, nullptr, batch, count, eps, y, stats, part, nullptr, st)
+                                      : launch_ln<false>(x, nullptr, batch, count, eps, y, stats, part, nullptr, st);
 }
 
 hipError_t launch_layer_norm_backward(const float* g, const float* y, const float2* stats, int batch,
                                       long long count, float* dx, float2* part, float2* stats2, hipStream_t st) {
   if (batch < 1 || batch > 65535 || count < 1 || ln_chunks(count) > (1 << 30)) return hipErrorInvalidValue;
-  const int nchunks = (int)ln_chunks(count);
-  hipLaunchKernelGGL(ln_partial_kernel, dim3(nchunks, batch), dim3(kLnThreads), 0, st, y, g, count, nchunks, part);
-  hipLaunchKernelGGL(ln_combine_kernel, dim3((batch + 63) / 64), dim3(64), 0, st, part, batch, count, nchunks, 0.f, 1,
-                     stats2);
-  hipLaunchKernelGGL(ln_apply_kernel, dim3(ln_apply_blocks((size_t)batch * count)), dim3(256), 0, st, y, g, stats,
-                     stats2, batch, count, dx);
-  return hipGetLastError();
+  float2* s = const_cast<float2*>(stats);  // (only read in this direction)
+  return ln_vec(g, y, dx, count) ? launch_ln<true>(y, g, batch, count, 0.f, dx, s, part, stats2, st)
+                                 : launch_ln<false>(y, g, batch, count, 0.f, dx, s, part, stats2, st);
 }
 
 hipError_t launch_prep_layers(const float* phi, int layers, int n, float gamma, const int* orient_host, SlotMap sm,
@@ -772,20 +923,35 @@ hipError_t launch_codesign(const float* logits, const float* noise, const float*
                            float tau, int hard, const float* grad_phi, float* phi_or_grad, hipStream_t st) {
   if (K < 1 || K > kCodesignMaxLevels) return hipErrorInvalidValue;
   if (count <= 0) return hipSuccess;
-  long long blocks = (count + 3) / 4;  // four pixels (waves) per workgroup
-  if (blocks > 65536) blocks = 65536;
-  const unsigned nb = (unsigned)blocks;
-  // registers per lane for the scores: ceil(K / 64) (K <= 1024)
-  switch ((K + 63) / 64) {
-    case 1: launch_codesign_ni<1>(logits, noise, levels, K, count, tau, hard, grad_phi, phi_or_grad, nb, st); break;
-    case 2: launch_codesign_ni<2>(logits, noise, levels, K, count, tau, hard, grad_phi, phi_or_grad, nb, st); break;
-    case 3:
-    case 4: launch_codesign_ni<4>(logits, noise, levels, K, count, tau, hard, grad_phi, phi_or_grad, nb, st); break;
-    case 5:
-    case 6:
-    case 7:
-    case 8: launch_codesign_ni<8>(logits, noise, levels, K, count, tau, hard, grad_phi, phi_or_grad, nb, st); break;
-    default: launch_codesign_ni<16>(logits, noise, levels, K, count, tau, hard, grad_phi, phi_or_grad, nb, st); break;
+  const CodesignArgs a{logits, noise, levels, K, count, 1.f / tau, hard, grad_phi, phi_or_grad, st};
+  auto aligned = [](const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; };
+  // 16-byte pieces: rows of K floats start on 16 bytes when the arrays do and K
+  // is a multiple of 4 (the phases and dL/dphi are read and written singly)
+  const bool vec = K % 4 == 0 && aligned(logits) && aligned(noise) && aligned(levels) &&
+                   (!grad_phi || aligned(phi_or_grad));
+  const int units = vec ? K / 4 : K;
+  if (vec) {
+    if (units <= 1) launch_codesign_shape<1, 1, true, 2>(a);
+    else if (units <= 2) launch_codesign_shape<2, 1, true, 2>(a);
+    else if (units <= 4) launch_codesign_shape<4, 1, true, 2>(a);
+    else if (units <= 8) launch_codesign_shape<8, 1, true, 2>(a);
+    else if (units <= 16) launch_codesign_shape<16, 1, true, 2>(a);
+    else if (units <= 32) launch_codesign_shape<32, 1, true, 2>(a);
+    else if (units <= 64) launch_codesign_shape<64, 1, true, 2>(a);
+    else if (units <= 128) launch_codesign_shape<64, 2, true, 2>(a);
+    else launch_codesign_shape<64, 4, true, 1>(a);
+  } else {
+    if (units <= 1) launch_codesign_shape<1, 1, false, 2>(a);
+    else if (units <= 2) launch_codesign_shape<2, 1, false, 2>(a);
+    else if (units <= 4) launch_codesign_shape<4, 1, false, 2>(a);
+    else if (units <= 8) launch_codesign_shape<8, 1, false, 2>(a);
+    else if (units <= 16) launch_codesign_shape<16, 1, false, 2>(a);
+    else if (units <= 32) launch_codesign_shape<32, 1, false, 2>(a);
+    else if (units <= 64) launch_codesign_shape<64, 1, false, 2>(a);
+    else if (units <= 128) launch_codesign_shape<64, 2, false, 2>(a);
+    else if (units <= 256) launch_codesign_shape<64, 4, false, 2>(a);
+    else if (units <= 512) launch_codesign_shape<64, 8, false, 1>(a);
+    else launch_codesign_shape<64, 16, false, 1>(a);
   }
   return hipGetLastError();
 }
