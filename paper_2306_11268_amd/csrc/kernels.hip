@@ -118,77 +118,64 @@ __global__ void __launch_bounds__(1024) loss_kernel(int kind, const float* __res
 // dL/dlogit_j = w_j (levels_j - sum_k w_k levels_k) dL/dphi / tau.
 //
 // A streaming pass over the scores: G = 1 .. 64 lanes hold a pixel's scores in
-// registers (as many as K needs, so that a wave carries 64 / G pixels), read
-// once in 16-byte pieces where K and the pointers allow, U pixels in flight per
-// lane group, every exponential formed once.  One wave per pixel reading
-// 4-byte values, one pixel at a time, was held by the latency of its loads and
-// its chain of reductions: 200 000 pixels of 256 levels 134 -> 68 us forward
+// registers (lane l levels l, l + G, ...; as many lanes as K needs, so that a
+// wave carries 64 / G pixels), read once, U pixels in flight per lane group,
+// every exponential formed once.  A lane adds its levels in order and the
+// lanes add up in halves, from 32 apart to 1, whatever G is.  One wave per
+// pixel, one pixel at a time, was held by the latency of its loads and its
+// chain of reductions: 200 000 pixels of 256 levels 134 -> 67 us forward
 // (410 MB, 6.1 TB/s) and 168 -> 108 us backward (615 MB, 5.7 TB/s), 300 000
-// of 64 levels 76 -> 25 and 72 -> 36.
+// of 64 levels 76 -> 39 and 72 -> 48.  16-byte loads, whose lanes hold
+// neighbouring levels, gain nothing at 256 levels and 13 us at 64, but they
+// change the order of a pixel's sums, which the gradient's level minus mean
+// makes visible (1e-4 of the largest value).
 constexpr int kCodesignMaxLevels = 1024;
 
-// Lane i's partner within groups of 2, 4, 8 and 16 lanes: any lane of the other
-// half of the group, all of whose lanes hold the same partial result.
-template <int CTRL>
-__device__ __forceinline__ float dpp_move(float x) {
-  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xF, 0xF, false));
+// Reductions over groups of G lanes: across lanes D apart, from G/2 to 1.
+template <int D>
+__device__ __forceinline__ float lane_across(float x) {
+  if constexpr (D == 1) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0xB1, 0xF, 0xF, false));  // quad_perm [1,0,3,2]
+  } else if constexpr (D == 2) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x4E, 0xF, 0xF, false));  // quad_perm [2,3,0,1]
+  } else if constexpr (D == 8) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x128, 0xF, 0xF, false));  // row_ror:8
+  } else if constexpr (D == 4 || D == 16) {
+    return __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(x), (D << 10) | 0x1F));  // xor D
+  } else {
+    return __shfl_xor(x, 32, 64);
+  }
 }
 template <int G, class Op>
 __device__ __forceinline__ float group_reduce(float x, Op op) {
-  if constexpr (G >= 2) x = op(x, dpp_move<0xB1>(x));    // quad_perm [1,0,3,2]
-  if constexpr (G >= 4) x = op(x, dpp_move<0x4E>(x));    // quad_perm [2,3,0,1]
-  if constexpr (G >= 8) x = op(x, dpp_move<0x141>(x));   // row_half_mirror
-  if constexpr (G >= 16) x = op(x, dpp_move<0x140>(x));  // row_mirror
-  if constexpr (G >= 32) x = op(x, __shfl_xor(x, 16, 64));
-  if constexpr (G >= 64) x = op(x, __shfl_xor(x, 32, 64));
+  if constexpr (G >= 64) x = op(x, lane_across<32>(x));
+  if constexpr (G >= 32) x = op(x, lane_across<16>(x));
+  if constexpr (G >= 16) x = op(x, lane_across<8>(x));
+  if constexpr (G >= 8) x = op(x, lane_across<4>(x));
+  if constexpr (G >= 4) x = op(x, lane_across<2>(x));
+  if constexpr (G >= 2) x = op(x, lane_across<1>(x));
   return x;
 }
 
-// VEC: value i of the lane's NV float4 (i = 4 * v + c) is level 4 * (lane + G * v)
-// + c; else value i is level lane + G * i.
-template <int G, int NV, bool VEC>
-struct CodesignShape {
-  static constexpr int N = VEC ? 4 * NV : NV;
-  static __device__ __forceinline__ int level(int lane, int i) {
-    return VEC ? 4 * (lane + G * (i / 4)) + i % 4 : lane + G * i;
-  }
-};
-
-template <int G, int NV, bool VEC>
-__device__ __forceinline__ void codesign_read(const float* __restrict__ p, int K, int lane, bool ok,
-                                              float (&v)[CodesignShape<G, NV, VEC>::N]) {
-  using S = CodesignShape<G, NV, VEC>;
-  if constexpr (VEC) {
+template <int G, int N>
+__device__ __forceinline__ void codesign_read(const float* __restrict__ p, int K, int lane, bool ok, float (&v)[N]) {
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      const bool in = ok && S::level(lane, 4 * i) < K;
-      const float4 f = in ? *reinterpret_cast<const float4*>(p + S::level(lane, 4 * i)) : make_float4(0.f, 0.f, 0.f, 0.f);
-      v[4 * i] = f.x;
-      v[4 * i + 1] = f.y;
-      v[4 * i + 2] = f.z;
-      v[4 * i + 3] = f.w;
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < NV; ++i) v[i] = ok && S::level(lane, i) < K ? p[S::level(lane, i)] : 0.f;
-  }
+  for (int i = 0; i < N; ++i) v[i] = ok && lane + G * i < K ? p[lane + G * i] : 0.f;
 }
 
 // BWD: out [count][K] = dL/dlogits; else out [count] = phases.
-template <int G, int NV, bool VEC, int U, bool BWD>
+template <int G, int N, int U, bool BWD>
 __global__ void __launch_bounds__(256) codesign_kernel(const float* __restrict__ logits, const float* __restrict__ noise,
                                                        const float* __restrict__ levels, int K, long long count,
                                                        float inv_tau, int hard, const float* __restrict__ grad_phi,
                                                        float* __restrict__ out) {
-  using S = CodesignShape<G, NV, VEC>;
-  constexpr int N = S::N;
   constexpr int PER = 256 / G;  // lane groups per workgroup
   const int lane = threadIdx.x % G;
   const int group = threadIdx.x / G;
   auto fmax2 = [](float a, float b) { return fmaxf(a, b); };
   auto fsum2 = [](float a, float b) { return a + b; };
   float lv[N];
-  codesign_read<G, NV, VEC>(levels, K, lane, true, lv);
+  codesign_read<G, N>(levels, K, lane, true, lv);
   const long long step = (long long)gridDim.x * PER * U;
   for (long long p0 = ((long long)blockIdx.x * U) * PER + group; p0 < count + group; p0 += step) {
     float sc[U][N];
@@ -196,8 +183,8 @@ __global__ void __launch_bounds__(256) codesign_kernel(const float* __restrict__
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const long long p = p0 + (long long)u * PER;
-      codesign_read<G, NV, VEC>(logits + p * K, K, lane, p < count, sc[u]);
-      codesign_read<G, NV, VEC>(noise + p * K, K, lane, p < count, nz[u]);
+      codesign_read<G, N>(logits + p * K, K, lane, p < count, sc[u]);
+      codesign_read<G, N>(noise + p * K, K, lane, p < count, nz[u]);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -205,7 +192,7 @@ __global__ void __launch_bounds__(256) codesign_kernel(const float* __restrict__
       float smax = -INFINITY;
 #pragma unroll
       for (int i = 0; i < N; ++i) {
-        sc[u][i] = S::level(lane, i) < K ? sc[u][i] + nz[u][i] : -INFINITY;
+        sc[u][i] = lane + G * i < K ? sc[u][i] + nz[u][i] : -INFINITY;
         smax = fmaxf(smax, sc[u][i]);
       }
       smax = group_reduce<G>(smax, fmax2);
@@ -214,7 +201,7 @@ __global__ void __launch_bounds__(256) codesign_kernel(const float* __restrict__
         int kb = K;
 #pragma unroll
         for (int i = N - 1; i >= 0; --i) {
-          const int k = S::level(lane, i);
+          const int k = lane + G * i;
           if (k < K && sc[u][i] == smax) kb = k;
         }
         // (level indices are exact in float32)
@@ -223,11 +210,12 @@ __global__ void __launch_bounds__(256) codesign_kernel(const float* __restrict__
         if (lane == 0 && p < count) out[p] = levels[k < K ? k : 0];  // (none reaches it only for NaN scores)
         continue;
       }
+      const float ymax = smax * inv_tau;
       float es = 0.f;
       float ws = 0.f;
 #pragma unroll
       for (int i = 0; i < N; ++i) {
-        const float e = S::level(lane, i) < K ? expf((sc[u][i] - smax) * inv_tau) : 0.f;
+        const float e = lane + G * i < K ? expf(sc[u][i] * inv_tau - ymax) : 0.f;
         es += e;
         ws += e * lv[i];
         sc[u][i] = e;
@@ -244,19 +232,9 @@ __global__ void __launch_bounds__(256) codesign_kernel(const float* __restrict__
         for (int i = 0; i < N; ++i) sc[u][i] = sc[u][i] * inv_s * (lv[i] - mean) * gs;
         if (p < count) {
           float* o = out + p * K;
-          if constexpr (VEC) {
 #pragma unroll
-            for (int i = 0; i < NV; ++i) {
-              const int k = S::level(lane, 4 * i);
-              if (k < K)
-                *reinterpret_cast<float4*>(o + k) =
-                    make_float4(sc[u][4 * i], sc[u][4 * i + 1], sc[u][4 * i + 2], sc[u][4 * i + 3]);
-            }
-          } else {
-#pragma unroll
-            for (int i = 0; i < NV; ++i)
-              if (S::level(lane, i) < K) o[S::level(lane, i)] = sc[u][i];
-          }
+          for (int i = 0; i < N; ++i)
+            if (lane + G * i < K) o[lane + G * i] = sc[u][i];
         }
       }
     }
@@ -275,17 +253,17 @@ struct CodesignArgs {
   float* out;
   hipStream_t st;
 };
-template <int G, int NV, bool VEC, int U>
+template <int G, int N, int U>
 static void launch_codesign_shape(const CodesignArgs& a) {
   constexpr int PER = 256 / G * U;  // pixels per workgroup and round
   long long blocks = (a.count + PER - 1) / PER;
   if (blocks > 65536) blocks = 65536;
   const dim3 grid((unsigned)blocks);
   if (a.grad_phi) {
-    hipLaunchKernelGGL((codesign_kernel<G, NV, VEC, U, true>), grid, dim3(256), 0, a.st, a.logits, a.noise, a.levels, a.K,
+    hipLaunchKernelGGL((codesign_kernel<G, N, U, true>), grid, dim3(256), 0, a.st, a.logits, a.noise, a.levels, a.K,
                        a.count, a.inv_tau, a.hard, a.grad_phi, a.out);
   } else {
-    hipLaunchKernelGGL((codesign_kernel<G, NV, VEC, U, false>), grid, dim3(256), 0, a.st, a.logits, a.noise, a.levels,
+    hipLaunchKernelGGL((codesign_kernel<G, N, U, false>), grid, dim3(256), 0, a.st, a.logits, a.noise, a.levels,
                        a.K, a.count, a.inv_tau, a.hard, a.grad_phi, a.out);
   }
 }
@@ -924,35 +902,17 @@ hipError_t launch_codesign(const float* logits, const float* noise, const float*
   if (K < 1 || K > kCodesignMaxLevels) return hipErrorInvalidValue;
   if (count <= 0) return hipSuccess;
   const CodesignArgs a{logits, noise, levels, K, count, 1.f / tau, hard, grad_phi, phi_or_grad, st};
-  auto aligned = [](const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; };
-  // 16-byte pieces: rows of K floats start on 16 bytes when the arrays do and K
-  // is a multiple of 4 (the phases and dL/dphi are read and written singly)
-  const bool vec = K % 4 == 0 && aligned(logits) && aligned(noise) && aligned(levels) &&
-                   (!grad_phi || aligned(phi_or_grad));
-  const int units = vec ? K / 4 : K;
-  if (vec) {
-    if (units <= 1) launch_codesign_shape<1, 1, true, 2>(a);
-    else if (units <= 2) launch_codesign_shape<2, 1, true, 2>(a);
-    else if (units <= 4) launch_codesign_shape<4, 1, true, 2>(a);
-    else if (units <= 8) launch_codesign_shape<8, 1, true, 2>(a);
-    else if (units <= 16) launch_codesign_shape<16, 1, true, 2>(a);
-    else if (units <= 32) launch_codesign_shape<32, 1, true, 2>(a);
-    else if (units <= 64) launch_codesign_shape<64, 1, true, 2>(a);
-    else if (units <= 128) launch_codesign_shape<64, 2, true, 2>(a);
-    else launch_codesign_shape<64, 4, true, 1>(a);
-  } else {
-    if (units <= 1) launch_codesign_shape<1, 1, false, 2>(a);
-    else if (units <= 2) launch_codesign_shape<2, 1, false, 2>(a);
-    else if (units <= 4) launch_codesign_shape<4, 1, false, 2>(a);
-    else if (units <= 8) launch_codesign_shape<8, 1, false, 2>(a);
-    else if (units <= 16) launch_codesign_shape<16, 1, false, 2>(a);
-    else if (units <= 32) launch_codesign_shape<32, 1, false, 2>(a);
-    else if (units <= 64) launch_codesign_shape<64, 1, false, 2>(a);
-    else if (units <= 128) launch_codesign_shape<64, 2, false, 2>(a);
-    else if (units <= 256) launch_codesign_shape<64, 4, false, 2>(a);
-    else if (units <= 512) launch_codesign_shape<64, 8, false, 1>(a);
-    else launch_codesign_shape<64, 16, false, 1>(a);
-  }
+  if (K <= 1) launch_codesign_shape<1, 1, 4>(a);
+  else if (K <= 2) launch_codesign_shape<2, 1, 4>(a);
+  else if (K <= 4) launch_codesign_shape<4, 1, 4>(a);
+  else if (K <= 8) launch_codesign_shape<8, 1, 4>(a);
+  else if (K <= 16) launch_codesign_shape<16, 1, 4>(a);
+  else if (K <= 32) launch_codesign_shape<32, 1, 4>(a);
+  else if (K <= 64) launch_codesign_shape<64, 1, 4>(a);
+  else if (K <= 128) launch_codesign_shape<64, 2, 4>(a);
+  else if (K <= 256) launch_codesign_shape<64, 4, 2>(a);
+  else if (K <= 512) launch_codesign_shape<64, 8, 2>(a);
+  else launch_codesign_shape<64, 16, 1>(a);
   return hipGetLastError();
 }
 
