@@ -342,9 +342,7 @@ PassArgs base_args(const lr_donn* net, int batch) {
   a.batch = batch;
   a.spg = 1;
   a.tab_sym = net->approx == LR_ANGULAR_SPECTRUM || net->approx == LR_FRAUNHOFER ? 1 : 0;
-  const double inv = 1.0 / (static_cast<double>(net->n_fft) * net->n_fft);
-  a.scale = static_cast<float>(inv);
-  a.scale_lo = static_cast<float>(inv - a.scale);
+  a.scale = static_cast<float>(1.0 / (static_cast<double>(net->n_fft) * net->n_fft));
   return a;
 }
 

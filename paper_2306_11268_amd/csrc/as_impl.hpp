@@ -476,12 +476,7 @@ __global__ void __launch_bounds__((AsCols<PL, T>::P), (AsCols<PL, T>::WAVES)) as
     phase<IT>();
     as_a_inverse<IT, HALF>(x, u);
     const Rsrc ro = make_rsrc(a.out + (size_t)b * n * N, (unsigned)(n * N) * 8u);
-    // 1/N^2 is a power of two or carries its rounding error along: the same
-    // factor in every hop, an error of up to 2.5e-8 would add up over them
-    auto scaled = [&](float v) { return (N & (N - 1)) == 0 ? v * a.scale : fmaf(v, a.scale, v * a.scale_lo); };
-    each([&](auto k, unsigned o, int so) {
-      bstore_so(ro, o, so, c2(scaled(u[k.value].x), scaled(u[k.value].y)));
-    });
+    each([&](auto k, unsigned o, int so) { bstore_so(ro, o, so, cscale(u[k.value], a.scale)); });
   }
 }
 

@@ -59,8 +59,7 @@ struct PassArgs {
   // transfer function H[ky][kx] (angular-spectrum path)
   const float2* tab;
   int conj_tab;
-  float scale;    // angular-spectrum column pass: factor of its output, 1/N^2 = scale + scale_lo
-  float scale_lo;
+  float scale;    // angular-spectrum column pass: factor of its output, 1/N^2
   // modulation gamma*exp(j*phi_l), oriented [q][vec] (separable path) or natural [y][x]
   const float2* mod;
   int conj_mod;
