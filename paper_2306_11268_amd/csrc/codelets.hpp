@@ -101,6 +101,34 @@ struct UnitScale {
   static constexpr double g(int) { return 1.0; }
 };
 
+// Unit factors, with the constant q1 of Dft5 moved to the neighbouring float
+// that brings the mean gain of the rounded matrix (mean of conj(W) W' over its
+// 25 entries) nearest to one.  With every constant rounded to nearest the gain
+// is 1 + 0.8e-8 (then 1 + 0.3e-8); it is the same in each transform of each hop, so it adds up
+// linearly where rounding of the data adds up as a square root, and in the 10-,
+// 20- and 40-point codelets no folded stage balances it (the 25-point one does,
+// to 4e-10, and keeps UnitScale).  Same instructions.
+struct UnitGain : UnitScale {
+  static constexpr float q1(double c1, double c2, double s1, double s2, float q, float q2) {
+    const double C1 = static_cast<float>(c1), C2 = static_cast<float>(c2);
+    const double S1 = static_cast<float>(s1), S2 = static_cast<float>(s2);
+    float best = q;
+    double least = 1.0;
+    for (int i = -1; i <= 1; ++i) {
+      const float v = q + static_cast<float>(i) * 0x1p-24f;  // q1 = s2/s1 lies in [1/2, 1)
+      const double even = 4.0 * (1.0 + 2.0 * (c1 * C1 + c2 * C2));
+      const double odd = 4.0 * (s1 * S1 + s2 * S1 * v) + 4.0 * (s2 * S2 + s1 * S2 * q2);
+      const double bias = (5.0 + even + odd) / 25.0 - 1.0;
+      const double mag = bias < 0.0 ? -bias : bias;
+      if (mag < least) {
+        least = mag;
+        best = v;
+      }
+    }
+    return best;
+  }
+};
+
 template <int SIGN, class G>
 struct Dft5 {
   LR_HD static void run(float2* a) {
@@ -121,7 +149,12 @@ struct Dft5 {
     const float2 b2 = c2(fmaf(e22, T2.x, fmaf(e21, T1.x, a[0].x)), fmaf(e22, T2.y, fmaf(e21, T1.y, a[0].y)));
     // s1 t3 + s2 t4 = k1 (T3 + q1 T4), s2 t3 - s1 t4 = k2 (T3 - q2 T4)
     constexpr double k1 = s1 * g1, k2 = s2 * g1;
-    constexpr float q1 = static_cast<float>(s2 * g2 / k1), q2 = static_cast<float>(s1 * g2 / k2);
+    constexpr float q2 = static_cast<float>(s1 * g2 / k2);
+    constexpr float q1 = [] {
+      constexpr float q = static_cast<float>(s2 * g2 / k1);
+      if constexpr (std::is_same_v<G, UnitGain>) return UnitGain::q1(c1, c2v, s1, s2, q, q2);
+      else return q;
+    }();
     const float2 v1 = c2(fmaf(q1, T4.x, T3.x), fmaf(q1, T4.y, T3.y));
     const float2 v2 = c2(fmaf(-q2, T4.x, T3.x), fmaf(-q2, T4.y, T3.y));
     // SIGN*i*k*v = (-SIGN*k*v.y, SIGN*k*v.x)
@@ -256,7 +289,7 @@ struct DftPFA {
       constexpr int p = decltype(pc)::value;
       float2 s[Q];
       static_for<0, Q>([&](auto qc) { s[qc.value] = a[(Q * p + P * qc.value) % N]; });
-      Dft<Q, SIGN>::run(s);
+      if constexpr (Q == 5) Dft5<SIGN, UnitGain>::run(s); else Dft<Q, SIGN>::run(s);
       static_for<0, Q>([&](auto kc) { t[p * Q + kc.value] = s[kc.value]; });
     });
     static_for<0, Q>([&](auto kc) {
