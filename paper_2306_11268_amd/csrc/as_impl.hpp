@@ -191,7 +191,8 @@ __global__ void __launch_bounds__(AsRows<PL>::P, (KIND == kAsRowBwdMid || KIND =
       });
       phase<IT>();
       float2 x[N1];
-      EX::to_vector(buf, s, ab, bb, y, x);
+      // (the last adjoint pass goes straight to the next sample's to_vector)
+      EX::template to_vector<ACC && !FWD_OUT>(buf, s, ab, bb, y, x);
       phase<IT>();
       as_a_inverse<IT, HALF>(x, u);
       phase<IT>();

@@ -50,8 +50,11 @@ struct Items {
 
 // Exchange of one vector's A-item (x) with its B-items (y).  The A side of
 // element k1 is buf[ab + SA*k1], the B side of element q of round ic
-// buf[bb[ic] + SQ*q].  Each lane rewrites only entries it read last, so
-// successive exchanges need no barrier between them.  SPLIT: one component
+// buf[bb[ic] + SQ*q].  A to_vector after a to_items, and the other way round,
+// rewrites only entries that the same lane read last and needs no barrier
+// between them.  A to_vector after a to_vector writes entries that other lanes
+// read on their A side: the first of them is called with AGAIN, which ends it
+// with a barrier.  SPLIT: one component
 // at a time through a float buffer (half the shared memory, three times the
 // barriers), else a float2 buffer.  s: the lane's slot (B-items).
 // SPARE: the workgroup has lanes that repeat item 0.
@@ -88,6 +91,7 @@ struct Exchange {
     // lanes that repeat an item read entries another lane rewrites next
     if constexpr ((REPEAT && !IT::FULL_ROUNDS) || SPARE) exchange_sync<P>();
   }
+  template <bool AGAIN = false>
   static __device__ __forceinline__ void to_vector(Elem* buf, int s, int ab, const int (&bb)[IB], const float2 (&y)[IB][N2],
                                                    float2 (&x)[N1]) {
     if constexpr (SPLIT) {
@@ -113,6 +117,7 @@ struct Exchange {
       exchange_sync<P>();
       static_for<0, N1>([&](auto k) { x[k.value] = buf[ab + SA * k.value]; });
     }
+    if constexpr (AGAIN) exchange_sync<P>();
   }
 };
 
