@@ -112,7 +112,9 @@ typedef struct lr_donn {
   lr_detector det;
   const lr_c64* d_H;    /* device [n_fft][n_fft], written by lr_tf_build for the same
                            wavelength / pixel_pitch / distance / approx / n_fft.
-                           The Fresnel path relies on its separability. */
+                           The Fresnel path relies on its separability, the
+                           angular-spectrum path on H[n_fft - ky] = H[ky]; the
+                           other approximations read every entry. */
   int32_t flags;        /* 0, or LR_ACCUMULATE and / or one of LR_LAYER_PASSES, LR_WHOLE_FIELD */
   const lr_c64* d_skip; /* NULL, or device [batch][n][n]: a field added to the
                            detector-plane field before the intensity, the sums,

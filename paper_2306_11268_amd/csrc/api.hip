@@ -341,7 +341,7 @@ PassArgs base_args(const lr_donn* net, int batch) {
   a.off = (net->n_fft - net->n) / 2;
   a.batch = batch;
   a.spg = 1;
-  a.tab_sym = net->approx == LR_ANGULAR_SPECTRUM || net->approx == LR_FRAUNHOFER ? 1 : 0;
+  a.tab_sym = net->approx == LR_ANGULAR_SPECTRUM ? 1 : 0;
   a.scale = static_cast<float>(1.0 / (static_cast<double>(net->n_fft) * net->n_fft));
   return a;
 }

@@ -80,8 +80,9 @@ struct PassArgs {
   // reads and writes whole output columns
   int spec_centred;
   // angular-spectrum column pass: the table is even in ky (H[N - ky] =
-  // H[ky], exact for the analytic angular-spectrum transfer function and the
-  // far-field table), so only its rows ky <= N/2 are read
+  // H[ky], exact for the analytic angular-spectrum transfer function), so
+  // only its rows ky <= N/2 are read (not for the far-field table, whose
+  // rows may carry a caller's own phase)
   int tab_sym;
   // field added to the detector-plane field before any output or seed is
   // formed (natural [B][n][n]; nullable): an optical skip connection
