@@ -222,11 +222,7 @@ __global__ void __launch_bounds__(AsRows<PL>::P, (KIND == kAsRowBwdMid || KIND =
       if (a.grad_int) {
         const Rsrc rg = make_rsrc(a.grad_int + (size_t)b * nn, (unsigned)nn * 4u);
         each(8, [&](auto k, unsigned o, int so) { u[k.value] = bload_so<2>(rud, o, so); });
-        each(4, [&](auto k, unsigned o, int so) {
-          // (zero, not 0 * U_D, where dL/dI is zero: U_D may be infinite or NaN there)
-          const float g = bload_f_so(rg, o, so);
-          u[k.value] = g != 0.f ? cscale(u[k.value], 2.f * g) : c2(0.f, 0.f);
-        });
+        each(4, [&](auto k, unsigned o, int so) { u[k.value] = cscale(u[k.value], 2.f * bload_f_so(rg, o, so)); });
       } else {
         const float* __restrict__ gs = a.grad_sums + (size_t)b * a.K;
         const unsigned long long vmask = vok ? a.row_mask[vec] : 0ull;
@@ -519,35 +515,23 @@ hipError_t launch_as_row(const PassArgs& a, hipStream_t st) {
   return launch_as_row<N, KIND, false>(a, st);
 }
 
-template <int N, bool FAR, bool HALF>
-hipError_t launch_as_cols(const PassArgs& args, hipStream_t st) {
+template <int N, bool FAR>
+hipError_t launch_as_col(const PassArgs& args, hipStream_t st) {
   using PL = typename AsPlanFor<N>::type;
   constexpr int T = AsColT<N>::T;
-  constexpr int P = AsCols<PL, T>::P;
-  constexpr int tiles = (N + T - 1) / T;
-  // a launch holds fewer than 2^32 threads: batches past that (of apertures a
-  // few rows high) go in several
-  constexpr int most = static_cast<int>(0xffffffffu / (static_cast<unsigned>(P) * tiles)) - 8;
   PassArgs a = args;
-  a.ntiles = tiles;
-  for (long long b = 0; b < args.batch; b += most) {
-    a.batch = static_cast<int>(std::min<long long>(most, args.batch - b));
-    a.workers = tiles * a.batch;
-    a.in = static_cast<const float2*>(args.in) + (size_t)b * a.n * N;
-    a.out = args.out + (size_t)b * (FAR ? N : a.n) * N;
-    hipLaunchKernelGGL((as_col_pass<PL, T, HALF, FAR>), dim3(8 * ((a.workers + 7) / 8)), dim3(P), 0, st, a);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
-}
-template <int N, bool FAR>
-hipError_t launch_as_col(const PassArgs& a, hipStream_t st) {
   if (a.batch < 1 || a.n < 1 || a.n > N || a.off != (N - a.n) / 2) return hipErrorInvalidValue;
+  a.ntiles = (N + T - 1) / T;
+  a.workers = a.ntiles * a.batch;
+  const dim3 grid(8 * ((a.workers + 7) / 8));
   if constexpr (as_half_plan<N>()) {
-    if (as_half<N>(a)) return launch_as_cols<N, FAR, true>(a, st);
+    if (as_half<N>(a)) {
+      hipLaunchKernelGGL((as_col_pass<PL, T, true, FAR>), grid, dim3(AsCols<PL, T>::P), 0, st, a);
+      return hipGetLastError();
+    }
   }
-  return launch_as_cols<N, FAR, false>(a, st);
+  hipLaunchKernelGGL((as_col_pass<PL, T, false, FAR>), grid, dim3(AsCols<PL, T>::P), 0, st, a);
+  return hipGetLastError();
 }
 
 template <int N>
