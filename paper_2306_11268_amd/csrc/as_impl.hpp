@@ -222,7 +222,11 @@ __global__ void __launch_bounds__(AsRows<PL>::P, (KIND == kAsRowBwdMid || KIND =
       if (a.grad_int) {
         const Rsrc rg = make_rsrc(a.grad_int + (size_t)b * nn, (unsigned)nn * 4u);
         each(8, [&](auto k, unsigned o, int so) { u[k.value] = bload_so<2>(rud, o, so); });
-        each(4, [&](auto k, unsigned o, int so) { u[k.value] = cscale(u[k.value], 2.f * bload_f_so(rg, o, so)); });
+        each(4, [&](auto k, unsigned o, int so) {
+          // (zero, not 0 * U_D, where dL/dI is zero: U_D may be infinite or NaN there)
+          const float g = bload_f_so(rg, o, so);
+          u[k.value] = g != 0.f ? cscale(u[k.value], 2.f * g) : c2(0.f, 0.f);
+        });
       } else {
         const float* __restrict__ gs = a.grad_sums + (size_t)b * a.K;
         const unsigned long long vmask = vok ? a.row_mask[vec] : 0ull;
