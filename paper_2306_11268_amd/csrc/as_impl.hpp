@@ -519,23 +519,35 @@ hipError_t launch_as_row(const PassArgs& a, hipStream_t st) {
   return launch_as_row<N, KIND, false>(a, st);
 }
 
-template <int N, bool FAR>
-hipError_t launch_as_col(const PassArgs& args, hipStream_t st) {
+template <int N, bool FAR, bool HALF>
+hipError_t launch_as_cols(const PassArgs& args, hipStream_t st) {
   using PL = typename AsPlanFor<N>::type;
   constexpr int T = AsColT<N>::T;
+  constexpr int P = AsCols<PL, T>::P;
+  constexpr int tiles = (N + T - 1) / T;
+  // a launch holds fewer than 2^32 threads: batches past that (of apertures a
+  // few rows high) go in several
+  constexpr int most = static_cast<int>(0xffffffffu / (static_cast<unsigned>(P) * tiles)) - 8;
   PassArgs a = args;
-  if (a.batch < 1 || a.n < 1 || a.n > N || a.off != (N - a.n) / 2) return hipErrorInvalidValue;
-  a.ntiles = (N + T - 1) / T;
-  a.workers = a.ntiles * a.batch;
-  const dim3 grid(8 * ((a.workers + 7) / 8));
-  if constexpr (as_half_plan<N>()) {
-    if (as_half<N>(a)) {
-      hipLaunchKernelGGL((as_col_pass<PL, T, true, FAR>), grid, dim3(AsCols<PL, T>::P), 0, st, a);
-      return hipGetLastError();
-    }
+  a.ntiles = tiles;
+  for (long long b = 0; b < args.batch; b += most) {
+    a.batch = static_cast<int>(std::min<long long>(most, args.batch - b));
+    a.workers = tiles * a.batch;
+    a.in = static_cast<const float2*>(args.in) + (size_t)b * a.n * N;
+    a.out = args.out + (size_t)b * (FAR ? N : a.n) * N;
+    hipLaunchKernelGGL((as_col_pass<PL, T, HALF, FAR>), dim3(8 * ((a.workers + 7) / 8)), dim3(P), 0, st, a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((as_col_pass<PL, T, false, FAR>), grid, dim3(AsCols<PL, T>::P), 0, st, a);
-  return hipGetLastError();
+  return hipSuccess;
+}
+template <int N, bool FAR>
+hipError_t launch_as_col(const PassArgs& a, hipStream_t st) {
+  if (a.batch < 1 || a.n < 1 || a.n > N || a.off != (N - a.n) / 2) return hipErrorInvalidValue;
+  if constexpr (as_half_plan<N>()) {
+    if (as_half<N>(a)) return launch_as_cols<N, FAR, true>(a, st);
+  }
+  return launch_as_cols<N, FAR, false>(a, st);
 }
 
 template <int N>

@@ -50,15 +50,15 @@ __device__ __forceinline__ void prep_mod_body(const float* __restrict__ phi, int
 // up to 256 tiles one load at a time (20 us for 1000 sums of 67 tiles).
 __global__ void __launch_bounds__(256) finish_sums_kernel(const float* __restrict__ part, int batch, int ntiles, int K,
                                                           float* __restrict__ sums, int accumulate) {
-  const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (i >= batch * K) return;
   const int lane = threadIdx.x & 63;
-  const int b = i / K;
-  const int k = i - b * K;
-  float s = 0.f;
-  for (int tl = lane; tl < ntiles; tl += 64) s += part[((size_t)b * ntiles + tl) * K + k];
-  s = wave_sum(s);
-  if (lane == 0) sums[i] = accumulate ? sums[i] + s : s;
+  for (unsigned i = blockIdx.x * 4 + (threadIdx.x >> 6); i < (unsigned)(batch * K); i += gridDim.x * 4) {
+    const unsigned b = i / K;
+    const int k = (int)(i - b * K);
+    float s = 0.f;
+    for (int tl = lane; tl < ntiles; tl += 64) s += part[((size_t)b * ntiles + tl) * K + k];
+    s = wave_sum(s);
+    if (lane == 0) sums[i] = accumulate ? sums[i] + s : s;
+  }
 }
 
 // Loss of the detector sums, averaged over the batch, and its gradient
@@ -885,8 +885,10 @@ hipError_t launch_prep_layers(const float* phi, int layers, int n, float gamma, 
 
 hipError_t launch_finish_sums(const float* part, int batch, int ntiles, int K, float* sums, int accumulate,
                               hipStream_t st) {
-  const int total = batch * K;
-  hipLaunchKernelGGL(finish_sums_kernel, dim3((total + 3) / 4), dim3(256), 0, st, part, batch, ntiles, K, sums,
+  // (a launch holds fewer than 2^32 threads; more sums than 2^22 workgroups of
+  // four take further rounds)
+  const unsigned blocks = std::min((static_cast<unsigned>(batch * K) + 3) / 4, 1u << 22);
+  hipLaunchKernelGGL(finish_sums_kernel, dim3(blocks), dim3(256), 0, st, part, batch, ntiles, K, sums,
                      accumulate);
   return hipGetLastError();
 }
