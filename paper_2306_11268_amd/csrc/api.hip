@@ -163,9 +163,9 @@ struct Layout {
   size_t chirp_x = 0, chirp_y = 0, mod = 0, w0 = 0, w1 = 0;
   size_t sums_part = 0, grad_sums = 0, dphi_part = 0, regions = 0, row_mask = 0, col_mask = 0, row_perm = 0,
          col_perm = 0, total = 0;
-  int ntiles_vec = 0;   // tiles over n vectors
-  int groups = 1;
-  int spg = 1;
+  size_t sums_bytes = 0;  // of sums_part
+  int ntiles_vec = 0;     // tiles over n vectors
+  int groups = 1;         // partials dphi_part holds per layer
 };
 
 int ceil_div(int a, int b) { return (a + b - 1) / b; }
@@ -173,12 +173,20 @@ int ceil_div(int a, int b) { return (a + b - 1) / b; }
 // The separable path alternates axes: pass p (1-based) runs along rows for odd p.
 Axis pass_axis(int p) { return (p & 1) ? lr::kRow : lr::kCol; }
 
+// The sizes are part of the interface: which batches fit a workspace of a given
+// size, and the fixed one of lr_propagate_noalloc, does not depend on how the
+// passes split their work.  They are counted in tiles of tile_shape, and on
+// the non-separable path they hold a table of N x N entries (its passes read
+// the caller's).  Passes with narrower tiles put what they need beyond that
+// where the call has room: partial sums in the work field that the
+// detector-plane pass leaves idle, dphi partials in the table's place.
 Layout make_layout(const lr_donn* net, int batch, int op) {
   Layout L;
   const int n = net->n;
   const int N = net->n_fft;
   const bool as = net->approx != LR_FRESNEL;  // the non-separable passes
-  L.ntiles_vec = ceil_div(n, as ? lr::as_row_tile(N) : lr::tile_shape(N, 0).T);
+  const int tiles = ceil_div(n, lr::tile_shape(N, 0).T);
+  L.ntiles_vec = as ? ceil_div(n, lr::as_row_tile(N)) : tiles;
   const size_t c64 = 8;
   const size_t nn = static_cast<size_t>(n) * n;
   const size_t field = static_cast<size_t>(batch) * (as ? static_cast<size_t>(n) * N : nn) * c64;
@@ -188,13 +196,10 @@ Layout make_layout(const lr_donn* net, int batch, int op) {
     off += align256(bytes);
     return at;
   };
+  const size_t table = as ? static_cast<size_t>(N) * N * c64 : 0;
   if (!as) {
     L.chirp_x = take(N * c64);
     L.chirp_y = take(N * c64);
-  } else {
-    // not used by the passes, which read the caller's table; part of the size
-    // so that which batches fit a fixed workspace does not change
-    take(static_cast<size_t>(N) * N * c64);
   }
   if (op != LR_OP_PROPAGATE) L.mod = take(static_cast<size_t>(net->num_layers) * nn * c64);
   L.w0 = take(field);
@@ -208,22 +213,22 @@ Layout make_layout(const lr_donn* net, int batch, int op) {
     L.col_perm = take(static_cast<size_t>(n) * 4);
   }
   if (op == LR_OP_FORWARD && K > 0) {
-    // (the detector-plane pass has its own tiles, of at least one vector)
-    const int tiles = as ? L.ntiles_vec
-                         : ceil_div(n, lr::fresnel_pass_tile(N, lr::kFwdLast, pass_axis(net->num_layers + 2), n == N));
-    L.sums_part = take(static_cast<size_t>(batch) * std::max(tiles, L.ntiles_vec) * K * 4);
+    L.sums_bytes = static_cast<size_t>(batch) * tiles * K * 4;
+    L.sums_part = take(L.sums_bytes);
   }
+  if (op == LR_OP_BACKWARD && K > 0) L.grad_sums = take(static_cast<size_t>(batch) * K * 4);
+  const size_t spare = take(table);
   if (op == LR_OP_BACKWARD) {
-    if (K > 0) L.grad_sums = take(static_cast<size_t>(batch) * K * 4);
-    const int work_tiles = L.ntiles_vec;
-    // (the angular-spectrum row passes run single waves: twice the workgroups)
-    int spg = ceil_div(batch * work_tiles, as ? 4096 : 2048);
+    int spg = ceil_div(batch * tiles, 2048);
     if (spg < 1) spg = 1;
     if (spg > batch) spg = batch > 0 ? batch : 1;
-    L.spg = spg;
     L.groups = batch > 0 ? ceil_div(batch, spg) : 1;
     // one set of partials per layer, reduced in a single launch at the end
-    L.dphi_part = take(static_cast<size_t>(net->num_layers) * L.groups * nn * 4);
+    const size_t per_group = static_cast<size_t>(net->num_layers) * nn * 4;
+    take(L.groups * per_group);
+    L.dphi_part = spare;
+    const int room = static_cast<int>(std::min<size_t>((off - spare) / per_group, static_cast<size_t>(std::max(batch, 1))));
+    L.groups = std::max(L.groups, room);
   }
   L.total = off;
   return L;
@@ -815,6 +820,17 @@ int lr_donn_forward(const lr_donn* net, int32_t batch, const float* d_amp, const
   a.accumulate = accumulate ? 1 : 0;
   a.full = slot_ordered(net) ? 1 : 0;
   int sum_tiles = L.ntiles_vec;  // tiles that wrote partial detector sums
+  // Partials [batch][tiles][K] of the detector-plane pass: their own part of the
+  // workspace, or (tiles narrower than those it is counted in) the work field the
+  // pass neither reads nor writes.  That is larger: only full apertures and the
+  // non-separable path have narrower tiles, a row of a field there is 8 N >= 512
+  // bytes, and the partials are at most 4 K <= 256 bytes a row.
+  float* sums_part = at<float>(d_work, L.sums_part);
+  auto place_sums = [&](int tiles, float2* idle) {
+    sum_tiles = tiles;
+    if (static_cast<size_t>(batch) * tiles * net->det.num * 4 > L.sums_bytes) sums_part = reinterpret_cast<float*>(idle);
+    return sums_part;
+  };
   const bool whole_field = net->approx == LR_FRESNEL && n == N && lr::field_forward_supported(N) &&
                            ((net->flags & LR_WHOLE_FIELD) || lr::field_forward_preferred(N, batch)) && !saved &&
                            (d_sums || d_intensity || d_field_out) && !net->d_skip &&
@@ -832,7 +848,7 @@ int lr_donn_forward(const lr_donn* net, int32_t batch, const float* d_amp, const
     fa.chirp_y = at<float2>(d_work, L.chirp_y);
     if (d_sums) {
       fa.reg = host_regions(net->det);
-      fa.sums_part = at<float>(d_work, L.sums_part);
+      fa.sums_part = place_sums(1, nullptr);
     }
     fa.intensity = d_intensity;
     fa.field_out = reinterpret_cast<float2*>(d_field_out);
@@ -841,7 +857,6 @@ int lr_donn_forward(const lr_donn* net, int32_t batch, const float* d_amp, const
     char name[48];
     std::snprintf(name, sizeof name, "field_forward_N%d", N);
     LR_TRY(run_timed(name, st, [&] { return lr::launch_field_forward(N, fa, st); }));
-    sum_tiles = 1;
   } else if (net->approx == LR_FRESNEL) {
     a.nvec = n;
     a.ntiles = L.ntiles_vec;
@@ -880,11 +895,10 @@ int lr_donn_forward(const lr_donn* net, int32_t batch, const float* d_amp, const
       d.skip = reinterpret_cast<const float2*>(net->d_skip);
       if (d_sums) {
         set_detector(d, net->det, L, d_work);
-        d.sums_part = at<float>(d_work, L.sums_part);
         // sums only: transform just the rows / columns the regions cover
         if (!d_intensity && !d_field_out) restrict_to_regions(d, net->det, L, d_work, ax, tile_t, false);
+        d.sums_part = place_sums(d.ntiles, w[saved ? 0 : (Lyr & 1) ^ 1]);
       }
-      sum_tiles = d.ntiles;
       LR_TRY(fr_pass(N, lr::kFwdLast, ax, d, st));
     }
   } else {
@@ -918,7 +932,7 @@ int lr_donn_forward(const lr_donn* net, int32_t batch, const float* d_amp, const
         r.saved_ud = saved ? saved + static_cast<size_t>(Lyr) * batch * nn : nullptr;
         if (d_sums) {
           set_detector(r, net->det, L, d_work);
-          r.sums_part = at<float>(d_work, L.sums_part);
+          r.sums_part = place_sums(L.ntiles_vec, w[cur ^ 1]);
         }
         LR_TRY(as_pass(N, lr::kAsRowLast, r, st));
       }
@@ -926,7 +940,7 @@ int lr_donn_forward(const lr_donn* net, int32_t batch, const float* d_amp, const
   }
   if (d_sums) {
     LR_TRY(run_timed("finish_sums", st, [&] {
-      return lr::launch_finish_sums(at<float>(d_work, L.sums_part), batch, sum_tiles, net->det.num, d_sums,
+      return lr::launch_finish_sums(sums_part, batch, sum_tiles, net->det.num, d_sums,
                                     accumulate ? 1 : 0, st);
     }));
   }
@@ -1039,7 +1053,6 @@ int lr_donn_backward(const lr_donn* net, int32_t batch, const float* d_phi, cons
     for (int l = Lyr; l >= 1; --l) {
       const Axis ax = pass_axis(l + 1);
       PassArgs m = a;
-      m.spg = L.spg;
       m.in = w[cur];
       m.tab = chirp(ax);
       m.mod = ws_mod + static_cast<size_t>(l - 1) * nn;
