@@ -3,10 +3,10 @@
 // A hop is FFT_x of every row, then per column FFT_y, x H, IFFT_y, then IFFT_x
 // of every row.  Between passes a sample is stored as n rows of N x-spectrum
 // values in natural frequency order ([B][n][N]); only the n rows inside the
-// aperture carry data.  Positions and frequencies are natural at every size
-// (AsPlanFor), so a lane's elements lie at one per-lane base plus
+// aperture carry data.  With the Cooley-Tukey plans (AsPlanFor) positions and
+// frequencies are natural, so a lane's elements lie at one per-lane base plus
 // compile-time offsets in every array a pass touches, and no array is staged
-// through shared memory:
+// through shared memory (350 points: the last paragraph):
 //
 //   A-item j of a vector: positions j + N2*k, k < N1;
 //   B-item k1: frequencies k1 + N1*k2, k2 < N2, and on its other side the
@@ -29,6 +29,12 @@
 // With a field zero padded to twice its size (HALF: n = N/2, N1 divisible by
 // 4) a lane's elements inside the aperture are exactly k = N1/4 .. 3*N1/4 - 1:
 // the A-step runs HalfDft, and half of the loads, stores and products vanish.
+//
+// 350 points keep their Good-Thomas plan: the twiddles of 25 x 14 added 7% to
+// the rounding error of a transform (9.4e-8 -> 1.01e-7).  Rows then move as
+// natural runs and take the plan's order through the exchange area; columns
+// address their rows and table rows one by one.  5 layers, batch 64: 511 -> 475 us
+// against 25 x 14 with twiddles (a single hop 101 -> 104).
 #pragma once
 
 #include "exchange.hpp"
@@ -38,7 +44,17 @@ namespace lr {
 
 template <class PL, bool FENCED = false>
 struct AsItems : Items<PL, FENCED> {
-  static_assert(!PL::PFA, "natural order");
+  // frequency of element k2 of item k1: freq_at<k2>(freq_base(k1))
+  static __device__ __forceinline__ int freq_base(int k1) { return PL::PFA ? k1 * PL::E1 % PL::N : k1; }
+  template <int K2>
+  static __device__ __forceinline__ int freq_at(int base) {
+    if constexpr (PL::PFA) {
+      const int f = base + K2 * PL::E2 % PL::N;
+      return f >= PL::N ? f - PL::N : f;
+    } else {
+      return base + PL::N1 * K2;
+    }
+  }
   // elements of an A-item inside a half aperture (HALF), or all of them
   static constexpr int K0(bool half) { return half ? PL::N1 / 4 : 0; }
   static constexpr int KN(bool half) { return half ? PL::N1 / 2 : PL::N1; }
@@ -77,6 +93,7 @@ struct AsRows : AsItems<PL> {
   static constexpr int R = (IT::N2 <= 32 ? 64 : 256) / IT::N2;
   static constexpr int P = (R * IT::N2 + 63) / 64 * 64;
   static constexpr bool SPARE = P != R * IT::N2 && P > 64;
+  static_assert(!SPARE || !PL::PFA, "spare lanes hold no run of a row");
   // row pitch: at least the exchange area, and = N2 mod 64, so that the rows
   // of a wave tile the banks on the A side
   static constexpr int PR = IT::N1 * IT::P1 + (64 + IT::N2 - IT::N1 * IT::P1 % 64) % 64;
@@ -163,6 +180,54 @@ __global__ void __launch_bounds__(AsRows<PL>::P, (KIND == kAsRowBwdMid || KIND =
     auto spec_base = [&](bool ok, int ic) -> unsigned {
       return ok ? (unsigned)(vec * N + IT::template item_of<true>(s, ic)) * 8u : kOutOfRange;
     };
+    // Good-Thomas plans: arrays move as runs j + N2*m, m < N1, in natural order
+    // (consecutive lanes, consecutive values) and take the plan's order through
+    // the row's exchange area, one component at a time.
+    [[maybe_unused]] auto reorder = [&](auto&& write, auto&& read) {
+      if constexpr (PL::PFA) {
+        float* const line = reinterpret_cast<float*>(buf) + r * W::PR;
+        static_for<0, 2>([&](auto c) {
+          exchange_sync<W::P>();
+          write(c, line);
+          exchange_sync<W::P>();
+          read(c, line);
+        });
+        exchange_sync<W::P>();
+      }
+    };
+    auto run_write = [&](float2* v) {
+      return [v, j](auto c, float* line) {
+        static_for<0, N1>([&](auto m) { line[j + N2 * m.value] = c.value ? v[m.value].y : v[m.value].x; });
+      };
+    };
+    auto run_read = [&](float2* v) {
+      return [v, j](auto c, float* line) {
+        static_for<0, N1>([&](auto m) {
+          const float f = line[j + N2 * m.value];
+          if constexpr (c.value) v[m.value].y = f; else v[m.value].x = f;
+        });
+      };
+    };
+    // a run of positions into A-item order, and back
+    auto to_item = [&](float2(&v)[KN]) {
+      if constexpr (PL::PFA) {
+        const int p0 = PL::pos_base(opaque<IT>(j));
+        reorder(run_write(v), [&](auto c, float* line) {
+          static_for<0, N1>([&](auto k) {
+            const float f = line[PL::pos_at(p0, k.value)];
+            if constexpr (c.value) v[k.value].y = f; else v[k.value].x = f;
+          });
+        });
+      }
+    };
+    auto to_run = [&](float2(&v)[KN]) {
+      if constexpr (PL::PFA) {
+        const int p0 = PL::pos_base(opaque<IT>(j));
+        reorder([&](auto c, float* line) {
+          static_for<0, N1>([&](auto k) { line[PL::pos_at(p0, k.value)] = c.value ? v[k.value].y : v[k.value].x; });
+        }, run_read(v));
+      }
+    };
     if constexpr (KIND == kAsRowLast) {
       // sums only: rows no region covers contribute nothing
       if (!a.intensity && !a.field_out && !a.saved_ud) {
@@ -181,10 +246,26 @@ __global__ void __launch_bounds__(AsRows<PL>::P, (KIND == kAsRowBwdMid || KIND =
     if constexpr (SPECTRAL_IN) {
       const Rsrc rin = make_rsrc(static_cast<const float2*>(a.in) + (size_t)b * n * N, (unsigned)(n * N) * 8u);
       float2 y[IB][N2];
-      static_for<0, IB>([&](auto ic) {
-        const unsigned base = spec_base(vec < n, ic.value);
-        static_for<0, N2>([&](auto k2) { y[ic.value][k2.value] = bload_so<2>(rin, base, N1 * 8 * k2.value); });
-      });
+      if constexpr (PL::PFA) {
+        float2 run[N1];
+        const unsigned base = vec < n ? (unsigned)(vec * N + j) * 8u : kOutOfRange;
+        static_for<0, N1>([&](auto m) { run[m.value] = bload_so<2>(rin, base, N2 * 8 * m.value); });
+        const int jb = opaque<IT>(s);
+        reorder(run_write(run), [&](auto c, float* line) {
+          static_for<0, IB>([&](auto ic) {
+            const int fb = IT::freq_base(IT::template item_of<true>(jb, ic.value));
+            static_for<0, N2>([&](auto k2) {
+              const float f = line[IT::template freq_at<k2.value>(fb)];
+              if constexpr (c.value) y[ic.value][k2.value].y = f; else y[ic.value][k2.value].x = f;
+            });
+          });
+        });
+      } else {
+        static_for<0, IB>([&](auto ic) {
+          const unsigned base = spec_base(vec < n, ic.value);
+          static_for<0, N2>([&](auto k2) { y[ic.value][k2.value] = bload_so<2>(rin, base, N1 * 8 * k2.value); });
+        });
+      }
       const int ji = opaque<IT>(s);
       static_for<0, IB>([&](auto ic) {
         item_inverse<IT>(IT::template item_of<true>(ji, ic.value), y[ic.value]);
@@ -196,6 +277,7 @@ __global__ void __launch_bounds__(AsRows<PL>::P, (KIND == kAsRowBwdMid || KIND =
       phase<IT>();
       as_a_inverse<IT, HALF>(x, u);
       phase<IT>();
+      to_run(u);
       if constexpr (KIND == kAsRowMid || ACC) {
         const Rsrc rmod = make_rsrc(a.mod, (unsigned)nn * 8u);
         if constexpr (KIND == kAsRowMid) {
@@ -256,6 +338,7 @@ __global__ void __launch_bounds__(AsRows<PL>::P, (KIND == kAsRowBwdMid || KIND =
 
     if constexpr (FWD_OUT) {
       phase<IT>();
+      to_item(u);
       float2 x[N1];
       as_a_forward<IT, HALF>(u, x);
       phase<IT>();
@@ -266,7 +349,25 @@ __global__ void __launch_bounds__(AsRows<PL>::P, (KIND == kAsRowBwdMid || KIND =
       const Rsrc ro = make_rsrc(a.out + (size_t)b * n * N, (unsigned)(n * N) * 8u);
       // centred: position p holds frequency (p + N/2) mod N, a rotation of k2 by N2/2
       const int rot = a.spec_centred ? N * 4 : 0;
-      static_for<0, IB>([&](auto ic) {
+      if constexpr (PL::PFA) {
+        static_for<0, IB>([&](auto ic) { item_forward<IT>(IT::template item_of<true>(jf, ic.value), y[ic.value]); });
+        float2 run[N1];
+        reorder([&](auto c, float* line) {
+          static_for<0, IB>([&](auto ic) {
+            const int fb = IT::freq_base(IT::template item_of<true>(jf, ic.value));
+            static_for<0, N2>([&](auto k2) {
+              line[IT::template freq_at<k2.value>(fb)] = c.value ? y[ic.value][k2.value].y : y[ic.value][k2.value].x;
+            });
+          });
+        }, run_read(run));
+        const unsigned base = (unsigned)(vec * N + j) * 8u;
+        static_for<0, N1>([&](auto m) {
+          constexpr int f = N2 * decltype(m)::value;  // frequency j + f
+          const bool low = f + N2 <= N / 2 || (f < N / 2 && j + f < N / 2);
+          const unsigned at = base + (unsigned)(f * 8 + (low ? rot : -rot));
+          bstore_so(ro, vok && act ? at : kOutOfRange, 0, run[m.value]);
+        });
+      } else static_for<0, IB>([&](auto ic) {
         item_forward<IT>(IT::template item_of<true>(jf, ic.value), y[ic.value]);
         const unsigned base = spec_base(vok && act && IT::item(jf, ic.value), ic.value);
         static_for<0, N2>([&](auto k2) {
@@ -426,8 +527,9 @@ __global__ void __launch_bounds__((AsCols<PL, T>::P), (AsCols<PL, T>::WAVES)) as
       const unsigned base = vok ? (unsigned)(jj * N + vec) * 8u : kOutOfRange;
       static_for<0, KN>([&](auto k) { f(k, base, N2 * k.value * N * 8); });
     } else {
+      const int p0 = PL::pos_base(jj);
       static_for<0, KN>([&](auto k) {
-        const int q = jj + N2 * k.value - off;
+        const int q = PL::pos_at(p0, k.value) - off;
         f(k, vok && (unsigned)q < (unsigned)n ? (unsigned)(q * N + vec) * 8u : kOutOfRange, 0);
       });
     }
@@ -455,12 +557,20 @@ __global__ void __launch_bounds__((AsCols<PL, T>::P), (AsCols<PL, T>::WAVES)) as
     float2(&z)[N2] = y[ic.value];
     item_forward<IT>(k1, z);
     const bool col = vec < N;  // (spare lanes repeat an item, table and all)
+    const int fb = IT::freq_base(k1);
     const unsigned lo = col ? (unsigned)(k1 * N + kx) * 8u : kOutOfRange;
     const unsigned hi = col && sym ? (unsigned)((N1 - k1) * N + kx) * 8u : lo;
     static_for<0, N2>([&](auto k2) {
       constexpr int up = N1 * N * 8 * decltype(k2)::value;
       constexpr int down = N1 * N * 8 * (N2 - 1 - decltype(k2)::value);
-      const float2 h = k2.value < N2 / 2 ? bload_keep_so(rt, lo, up) : bload_keep_so(rt, hi, sym ? down : up);
+      float2 h;
+      if constexpr (PL::PFA) {
+        const int ky = IT::template freq_at<k2.value>(fb);
+        const int row = sym && ky > N / 2 ? N - ky : ky;
+        h = bload_keep_so(rt, col ? (unsigned)(row * N + kx) * 8u : kOutOfRange, 0);
+      } else {
+        h = k2.value < N2 / 2 ? bload_keep_so(rt, lo, up) : bload_keep_so(rt, hi, sym ? down : up);
+      }
       z[k2.value] = cmul(z[k2.value], c2(h.x, sg * h.y));
       if constexpr (k2.value % 8 == 7) phase<IT>();  // eight table values in flight
     });
@@ -468,8 +578,14 @@ __global__ void __launch_bounds__((AsCols<PL, T>::P), (AsCols<PL, T>::WAVES)) as
       const Rsrc ro = make_rsrc(a.out + (size_t)b * N * N, (unsigned)(N * N) * 8u);
       const unsigned out = vok ? (unsigned)(k1 * N + vec) * 8u : kOutOfRange;
       static_for<0, N2>([&](auto k2) {
-        constexpr int row = N1 * ((decltype(k2)::value + N2 / 2) % N2);  // (ky + N/2) mod N = k1 + row
-        bstore_so(ro, out, row * N * 8, z[k2.value]);
+        if constexpr (PL::PFA) {
+          const int ky = IT::template freq_at<k2.value>(fb);
+          const int row = ky < N / 2 ? ky + N / 2 : ky - N / 2;
+          bstore_so(ro, vok ? (unsigned)(row * N + vec) * 8u : kOutOfRange, 0, z[k2.value]);
+        } else {
+          constexpr int row = N1 * ((decltype(k2)::value + N2 / 2) % N2);  // (ky + N/2) mod N = k1 + row
+          bstore_so(ro, out, row * N * 8, z[k2.value]);
+        }
       });
     } else {
       phase<IT>();

@@ -121,16 +121,16 @@ struct RowPlanFor {
   using type = typename PlanFor<N>::type;
 };
 
-// Plans of the angular-spectrum passes: Cooley-Tukey at every length, so that
-// positions and frequencies are affine in the lane and element indices (rows
-// and spectra are then read and written straight from registers in natural
-// order), with the two factors as equal as the length allows (every lane of
-// the B-step has the same number of items: 20 x 20 at 400, where 25 x 16
-// leaves 7 of 16 lanes idle in the second round).
+// Plans of the angular-spectrum passes: Cooley-Tukey, so that positions and
+// frequencies are affine in the lane and element indices (rows and spectra are
+// then read and written straight from registers in natural order), with the
+// two factors as equal as the length allows (every lane of the B-step has the
+// same number of items: 20 x 20 at 400, where 25 x 16 leaves 7 of 16 lanes idle
+// in the second round).  350 has no such factors and keeps the Good-Thomas 25 x
+// 14: with twiddles it rounds 7% worse.
 template <int N> struct AsPlanFor { using type = typename PlanFor<N>::type; };
 template <> struct AsPlanFor<100> { using type = Plan2<10, 10, false>; };
 template <> struct AsPlanFor<200> { using type = Plan2<20, 10, false>; };
-template <> struct AsPlanFor<350> { using type = Plan2<25, 14, false>; };
 template <> struct AsPlanFor<400> { using type = Plan2<20, 20, false>; };
 
 }  // namespace lr

@@ -55,20 +55,21 @@ static bool plan(std::mt19937& g) {
   using PL = typename lr::AsPlanFor<N>::type;
   std::normal_distribution<double> nd;
   std::vector<cd> x(N), got(N);
-  std::vector<float2> v(N);
+  std::vector<float2> v(N), w(N);
   for (int i = 0; i < N; ++i) { v[i] = lr::c2((float)nd(g), (float)nd(g)); x[i] = cd(v[i].x, v[i].y); }
-  bool ok = !PL::PFA && PL::N == N;
+  // (natural order at every length but the Good-Thomas 350)
+  bool ok = PL::N == N && PL::PFA == (N == 350);
   for (int j = 0; j < PL::N2; ++j) {
     float2 a[PL::N1];
-    for (int k = 0; k < PL::N1; ++k) a[k] = v[j + PL::N2 * k];  // natural positions
+    for (int k = 0; k < PL::N1; ++k) a[k] = v[PL::PFA ? PL::pos(k, j) : j + PL::N2 * k];
     lr::Dft<PL::N1, -1>::run(a);
-    for (int k = 0; k < PL::N1; ++k) v[j + PL::N2 * k] = a[k];
+    for (int k = 0; k < PL::N1; ++k) w[j + PL::N2 * k] = a[k];
   }
   for (int k1 = 0; k1 < PL::N1; ++k1) {
     float2 b[PL::N2];
-    for (int j = 0; j < PL::N2; ++j) b[j] = lr::cmul(v[PL::N2 * k1 + j], PL::twiddle(k1, j));
+    for (int j = 0; j < PL::N2; ++j) b[j] = PL::PFA ? w[PL::N2 * k1 + j] : lr::cmul(w[PL::N2 * k1 + j], PL::twiddle(k1, j));
     lr::Dft<PL::N2, -1>::run(b);
-    for (int k2 = 0; k2 < PL::N2; ++k2) got[k1 + PL::N1 * k2] = cd(b[k2].x, b[k2].y);  // natural frequencies
+    for (int k2 = 0; k2 < PL::N2; ++k2) got[PL::PFA ? PL::freq(k1, k2) : k1 + PL::N1 * k2] = cd(b[k2].x, b[k2].y);
   }
   return ok & close("plan", N, got, dft(x, -1));
 }
