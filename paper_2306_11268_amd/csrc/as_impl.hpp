@@ -488,6 +488,8 @@ __global__ void __launch_bounds__((AsCols<PL, T>::P), (AsCols<PL, T>::WAVES)) as
   constexpr int N2 = W::N2;
   constexpr int IB = W::IB;
   constexpr int KN = W::KN(HALF);
+  using Scaled = ScaledRoots<PL, HALF>;
+  constexpr bool SCALED = Scaled::ON;  // 1/N^2 in the inverse roots, else on the output
   __shared__ typename EX::Elem buf[W::LDS];
 
   const int per = (int)gridDim.x >> 3;
@@ -589,7 +591,7 @@ __global__ void __launch_bounds__((AsCols<PL, T>::P), (AsCols<PL, T>::WAVES)) as
       });
     } else {
       phase<IT>();
-      item_inverse<IT>(k1, z);
+      item_inverse<IT, std::conditional_t<SCALED, Scaled, ItemRoots<PL>>>(k1, z);
     }
   });
   if constexpr (!FAR) {
@@ -597,7 +599,9 @@ __global__ void __launch_bounds__((AsCols<PL, T>::P), (AsCols<PL, T>::WAVES)) as
     phase<IT>();
     as_a_inverse<IT, HALF>(x, u);
     const Rsrc ro = make_rsrc(a.out + (size_t)b * n * N, (unsigned)(n * N) * 8u);
-    each([&](auto k, unsigned o, int so) { bstore_so(ro, o, so, cscale(u[k.value], a.scale)); });
+    each([&](auto k, unsigned o, int so) {
+      if constexpr (SCALED) bstore_so(ro, o, so, u[k.value]); else bstore_so(ro, o, so, cscale(u[k.value], a.scale));
+    });
   }
 }
 
@@ -614,11 +618,19 @@ template <> struct AsColT<200> { static constexpr int T = 25; };
 template <> struct AsColT<350> { static constexpr int T = 32; };
 template <> struct AsColT<500> { static constexpr int T = 12; };
 
-// n = N/2 centred and N1 divisible by 4: HalfDft.
+// n = N/2 centred and N1 divisible by 4: HalfDft.  Its roots add 2-4% to the
+// rounding of a transform at 20 values, where a whole transform has none
+// (Good-Thomas 4 x 5).  A hop at 400 makes up for it (ScaledRoots; 1.94e-7 before
+// half transforms, 1.92e-7 now, against 64 bits), one at 200 does not (1.77e-7
+// -> 1.83e-7), nor does the far field at 400 (1.33e-7 -> 1.36e-7).  These take whole
+// transforms: 100 in 200, 5 layers, batch 200, 263 -> 287 us; far field of 200 in
+// 400, batch 64, 38.6 -> 41.3 us.
 template <int N>
-constexpr bool as_half_plan() { return AsPlanFor<N>::type::N1 % 4 == 0; }
+constexpr bool as_half_plan() { return AsPlanFor<N>::type::N1 % 4 == 0 && N != 200; }
 template <int N>
-bool as_half(const PassArgs& a) { return as_half_plan<N>() && 2 * a.n == N && 4 * a.off == N; }
+bool as_half(const PassArgs& a, bool far) {
+  return as_half_plan<N>() && 2 * a.n == N && 4 * a.off == N && !(far && N == 400);
+}
 
 template <int N, int KIND, bool HALF>
 hipError_t launch_as_row(const PassArgs& a, hipStream_t st) {
@@ -630,7 +642,7 @@ template <int N, int KIND>
 hipError_t launch_as_row(const PassArgs& a, hipStream_t st) {
   if (a.workers < 1 || a.n < 1 || a.n > N || a.off != (N - a.n) / 2) return hipErrorInvalidValue;
   if constexpr (as_half_plan<N>()) {
-    if (as_half<N>(a)) return launch_as_row<N, KIND, true>(a, st);
+    if (as_half<N>(a, a.spec_centred != 0)) return launch_as_row<N, KIND, true>(a, st);
   }
   return launch_as_row<N, KIND, false>(a, st);
 }
@@ -661,7 +673,7 @@ template <int N, bool FAR>
 hipError_t launch_as_col(const PassArgs& a, hipStream_t st) {
   if (a.batch < 1 || a.n < 1 || a.n > N || a.off != (N - a.n) / 2) return hipErrorInvalidValue;
   if constexpr (as_half_plan<N>()) {
-    if (as_half<N>(a)) return launch_as_cols<N, FAR, true>(a, st);
+    if (as_half<N>(a, FAR)) return launch_as_cols<N, FAR, true>(a, st);
   }
   return launch_as_cols<N, FAR, false>(a, st);
 }

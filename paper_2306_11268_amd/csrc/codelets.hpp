@@ -103,11 +103,10 @@ struct UnitScale {
 
 // Unit factors, with the constant q1 of Dft5 moved to the neighbouring float
 // that brings the mean gain of the rounded matrix (mean of conj(W) W' over its
-// 25 entries) nearest to one.  With every constant rounded to nearest the gain
-// is 1 + 0.8e-8 (then 1 + 0.3e-8); it is the same in each transform of each hop, so it adds up
-// linearly where rounding of the data adds up as a square root, and in the 10-,
-// 20- and 40-point codelets no folded stage balances it (the 25-point one does,
-// to 4e-10, and keeps UnitScale).  Same instructions.
+// 25 entries) nearest to one: 1 + 0.3e-8, with every constant rounded to nearest
+// 1 + 0.8e-8.  It adds up linearly over the hops (root_gain), and in the 10-, 20-
+// and 40-point codelets no folded stage balances it (the 25-point one does, to
+// 4e-10, and keeps UnitScale).  Same instructions.
 struct UnitGain : UnitScale {
   static constexpr float q1(double c1, double c2, double s1, double s2, float q, float q2) {
     const double C1 = static_cast<float>(c1), C2 = static_cast<float>(c2);
@@ -146,7 +145,8 @@ struct Dft5 {
     constexpr float e11 = static_cast<float>(c1 * g1), e12 = static_cast<float>(c2v * g2);
     constexpr float e21 = static_cast<float>(c2v * g1), e22 = static_cast<float>(c1 * g2);
     const float2 b1 = c2(fmaf(e12, T2.x, fmaf(e11, T1.x, a[0].x)), fmaf(e12, T2.y, fmaf(e11, T1.y, a[0].y)));
-    const float2 b2 = c2(fmaf(e22, T2.x, fmaf(e21, T1.x, a[0].x)), fmaf(e22, T2.y, fmaf(e21, T1.y, a[0].y)));
+    // (the smaller product first: the sum rounded on the way is smaller)
+    const float2 b2 = c2(fmaf(e21, T1.x, fmaf(e22, T2.x, a[0].x)), fmaf(e21, T1.y, fmaf(e22, T2.y, a[0].y)));
     // s1 t3 + s2 t4 = k1 (T3 + q1 T4), s2 t3 - s1 t4 = k2 (T3 - q2 T4)
     constexpr double k1 = s1 * g1, k2 = s2 * g1;
     constexpr float q2 = static_cast<float>(s1 * g2 / k2);
@@ -350,15 +350,11 @@ struct HalfDft {
     Dft<H, 1>::run(o);
     static_for<0, H>([&](auto i) {
       constexpr int n = decltype(i)::value + Q;
-      if constexpr ((4 * n) % R == 0) {
-        x[n - Q] = cadd(e[n % H], twiddle_const<R, 1, n>(o[n % H]));
-      } else {
-        constexpr cdbl z = unit_root(n, R, 1);
-        constexpr float wr = static_cast<float>(z.re);
-        constexpr float wi = static_cast<float>(z.im);
-        const float2 u = o[n % H];
-        x[n - Q] = c2(fmaf(wr, u.x, fmaf(-wi, u.y, e[n % H].x)), fmaf(wr, u.y, fmaf(wi, u.x, e[n % H].y)));
-      }
+      // w^-n u = g (unit-scale root times u): what is rounded on the way is smaller
+      // than e + a part of w^-n u
+      constexpr float g = static_cast<float>(split_root_scale(n, R, 1));
+      const float2 u = split_root<R, 1, n>(o[n % H]);
+      x[n - Q] = c2(fmaf(g, u.x, e[n % H].x), fmaf(g, u.y, e[n % H].y));
     });
   }
 };

@@ -149,34 +149,53 @@ template <class PL>
 struct RootPairs {
   float4 w[PL::N2 / 2 * PL::N1];
 };
+// factor: of every entry, the exact ones included.
 template <class PL>
-constexpr RootPairs<PL> make_root_pairs() {
+constexpr RootPairs<PL> make_root_pairs(double factor) {
   RootPairs<PL> t{};
   for (int p = 0; p < PL::N2 / 2; ++p)
     for (int k1 = 0; k1 < PL::N1; ++k1) {
       const cdbl a = unit_root(static_cast<long long>(k1) * (2 * p), PL::N, -1);
       const cdbl b = unit_root(static_cast<long long>(k1) * (2 * p + 1), PL::N, -1);
       float4& e = t.w[p * PL::N1 + k1];
-      e.x = static_cast<float>(a.re);
-      e.y = static_cast<float>(a.im);
-      e.z = static_cast<float>(b.re);
-      e.w = static_cast<float>(b.im);
+      const double ga = factor * (k1 * p == 0 ? 1.0 : root_gain<PL::N>());
+      const double gb = factor * (k1 == 0 ? 1.0 : root_gain<PL::N>());
+      e.x = static_cast<float>(ga * a.re);
+      e.y = static_cast<float>(ga * a.im);
+      e.z = static_cast<float>(gb * b.re);
+      e.w = static_cast<float>(gb * b.im);
     }
   return t;
 }
 template <class PL>
 struct ItemRoots {
-  static constexpr RootPairs<PL> table = make_root_pairs<PL>();
+  static constexpr RootPairs<PL> table = make_root_pairs<PL>(1.0);
+};
+// The same over N^2, for the inverse transform of a hop: its factor then costs no
+// rounding of its own (and N1 products a lane less than on the output).  Where
+// 1/N^2 is a float there is nothing to gain, and plans without a table scale
+// the output.  The factor also takes out the mean gain of the hop's four
+// transforms (root_gain): 2.8e-8 at 100, 200 and 400 points, 5.2e-8 with half
+// transforms at 400, 2.4e-8 at 500.
+template <class PL, bool HALF>
+struct ScaledRoots {
+  static constexpr bool ON = !PL::PFA && PL::N2 < 32 && (PL::N & (PL::N - 1)) != 0;
+  static constexpr double gain = PL::N == 500 ? 2.4e-8 : HALF ? 5.2e-8 : 2.8e-8;
+  static constexpr double factor = (1.0 - gain) / ((double)PL::N * PL::N);
+  static constexpr RootPairs<PL> table = make_root_pairs<PL>(factor);
 };
 // Multiply a B-item by its twiddles (INV: their conjugates), eight values at a
 // time so that the roots are not all live at once.  Items of 32 or more values
 // take the products w^(k1*j) = w^(k1*(j mod 8)) * w^(8*k1*(j/8)) instead: 7 +
 // N2/8 - 1 loads, one more rounding (<= 1.5 ulp) (1000 points: column pass 133
 // against 155 us; 1024: row pass 93 against 96).
-template <class IT, bool INV>
+// Roots: the table, ItemRoots or ScaledRoots.
+template <class IT, bool INV, class Table = ItemRoots<typename IT::Plan>>
 __device__ __forceinline__ void item_twiddle(int k1, float2 (&y)[IT::N2]) {
   using PL = typename IT::Plan;
   constexpr int N2 = IT::N2;
+  constexpr bool SCALED = !std::is_same_v<Table, ItemRoots<PL>>;
+  static_assert(!SCALED || N2 < 32, "long items have no scaled table");
   if constexpr (N2 >= 32) {
     auto root = [&](int m) { return root_at<IT::N>(INV ? (unsigned)(IT::N - k1 * m) : (unsigned)(k1 * m)); };
     float2 lo[8];
@@ -194,10 +213,11 @@ __device__ __forceinline__ void item_twiddle(int k1, float2 (&y)[IT::N2]) {
     });
   } else static_for<0, N2 / 2>([&](auto pc) {
     constexpr int p = decltype(pc)::value;
-    const float4 w = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(ItemRoots<PL>::table.w) +
+    const float4 w = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(Table::table.w) +
                                                       (unsigned)(p * IT::N1 + k1) * 16u);
     auto times = [](float2 u, float2 r) { return INV ? cmulc(u, r) : cmul(u, r); };
     if constexpr (p > 0) y[2 * p] = times(y[2 * p], c2(w.x, w.y));
+    else if constexpr (SCALED) y[0] = cscale(y[0], static_cast<float>(Table::factor));
     y[2 * p + 1] = times(y[2 * p + 1], c2(w.z, w.w));
     if constexpr (p % 4 == 3) phase<IT>();
   });
@@ -211,12 +231,12 @@ __device__ __forceinline__ void item_forward(int k1, float2 (&y)[IT::N2]) {
   Dft<IT::N2, -1>::run(y);
   phase<IT>();
 }
-template <class IT>
+template <class IT, class Table = ItemRoots<typename IT::Plan>>
 __device__ __forceinline__ void item_inverse(int k1, float2 (&y)[IT::N2]) {
   Dft<IT::N2, 1>::run(y);
   phase<IT>();
   if constexpr (!IT::Plan::PFA) {
-    item_twiddle<IT, true>(opaque<IT>(k1), y);
+    item_twiddle<IT, true, Table>(opaque<IT>(k1), y);
     phase<IT>();
   }
 }

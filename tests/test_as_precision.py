@@ -14,7 +14,7 @@ import pytest
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 NATIVE = os.path.join(HERE, "native")
-SIZES = (350, 500, 1000)
+SIZES = (64, 100, 128, 200, 256, 350, 400, 500, 512, 1000, 1024)
 
 
 @pytest.mark.parametrize("n", SIZES)
