@@ -92,13 +92,15 @@ constexpr bool wave_tile_kind() {
 //   row layer passes: forward 16.3 -> 13.6 (64), 32 -> 24 (128), 64 -> 52 (256),
 //     84 -> 67 (400), 313 -> 280 (500), 145 -> 113 (1000), but 82 -> 84 (200);
 //     adjoint 22.4 -> 19.9 (64), 49.5 -> 42 (128), 127 -> 110 (200), 105 -> 95
-//     (256), 127 -> 99 (400), 231 -> 199 (1000), 440 -> 448 (500), but 42 -> 47
-//     (100: items of 4 values, seven rounds of them);
+//     (256), 127 -> 99 (400), 231 -> 199 (1000), but 42 -> 47 (100: items of 4
+//     values, seven rounds of them); even at 500, where one-wave tiles of its own
+//     kernel measured 442 next to the other passes of this table and these 445;
 //   first row pass: 20 -> 18 (128), 46 -> 39 (256), 57 -> 45 (400), 84 -> 63
 //     (1000), but 63 -> 65 (200) and 23 -> 27 (100), where the natural row is
-//     staged for short items;
+//     staged for short items, and even at 64;
 //   forward column pass: 30 -> 26 (100), 28 -> 25 (128), 78 -> 50 (256), 80 -> 71
-//     (400), 349 -> 301 (500), but 84 -> 86 (200) and even at 64;
+//     (400), 349 -> 301 (500), 136 -> 134 (1000), but 84 -> 86 (200), 122.5 -> 126
+//     (1024) and even at 64;
 //   adjoint column passes: 20 -> 19 (64), 132 -> 103 (256), 625 -> 580 (500),
 //     236 -> 215 (512), but 42 -> 44 (100), 134 -> 137 (200), 75 -> 83 (350), 111 ->
 //     118 (400), 236 -> 288 (1000) and even at 128 and 1024: there the tile
@@ -107,8 +109,9 @@ template <int N, int KIND, int AXIS>
 constexpr bool sep_kind() {
   constexpr bool SHORT = N == 100 || N == 200;
   if (KIND == kFwdLast || KIND == kBwdFirst) return AXIS == kRow;
-  if (AXIS == kRow) return KIND == kBwdMid ? N != 100 : KIND != kBwdLast && !SHORT;
-  if (KIND == kFwdMid) return N != 64 && N != 200;
+  if (AXIS == kRow && KIND == kBwdMid) return N != 100;
+  if (AXIS == kRow) return KIND != kBwdLast && !SHORT;
+  if (KIND == kFwdMid) return N != 64 && N != 200 && N != 1024;
   return (KIND == kBwdMid || KIND == kBwdLast) && (N == 64 || N == 256 || N == 500 || N == 512);
 }
 // Vectors per workgroup of those passes (rows: one wave, or four at 40 slots;
