@@ -245,7 +245,7 @@ T* at(void* base, size_t off) {
 }
 
 // Layer l (1-based) is modulated in pass l+1: transposed storage when that pass is a row pass,
-// except where those passes take row-major tables (full aperture, the longer plans).
+// except where those passes take row-major tables (full aperture, row_major_rows).
 int layer_transposed(const lr_donn* net, int l, bool backward) {
   if (net->approx != LR_FRESNEL) return 0;
   if (pass_axis(l + 1) != lr::kRow) return 0;

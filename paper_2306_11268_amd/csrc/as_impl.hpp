@@ -85,7 +85,7 @@ __device__ __forceinline__ void as_a_inverse(float2 (&x)[IT::N1], float2 (&u)[IT
 // A-item j of row r, consecutive lanes consecutive elements, so every access
 // of a wave covers N2 consecutive values of R rows.  R*N2 is one wave where
 // N2 allows (no barriers at all; 60 of 64 lanes at N2 = 10 and 20, 56 at 14),
-// 8 rows in five waves at N2 = 40.
+// 6 rows in four waves (240 of 256 lanes) at N2 = 40.
 // ---------------------------------------------------------------------------
 template <class PL>
 struct AsRows : AsItems<PL> {

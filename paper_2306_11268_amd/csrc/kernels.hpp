@@ -190,7 +190,8 @@ int as_row_tile(int N);
 int as_pass_slots(int N, AsPassKind kind, bool half);
 
 // Small helper kernels.
-// sums[b][k] = (accumulate ? sums[b][k] : 0) + the per-tile partial sums, in tile order.
+// sums[b][k] = (accumulate ? sums[b][k] : 0) + the per-tile partial sums, tiles l, l + 64, ...
+// by lane l and the lanes in a fixed order.
 hipError_t launch_finish_sums(const float* part, int batch, int ntiles, int K, float* sums, int accumulate,
                               hipStream_t st);
 // Loss of the detector sums (kind 0: softmax cross-entropy, 1: squared norm

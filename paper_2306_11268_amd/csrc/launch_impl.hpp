@@ -16,7 +16,7 @@ template <int N> struct TileT;
 template <> struct TileT<64>   { static constexpr int T = 16; };
 template <> struct TileT<100>  { static constexpr int T = 16; };
 template <> struct TileT<128>  { static constexpr int T = 16; };
-template <> struct TileT<200>  { static constexpr int T = 32; };  // detector-plane passes: 47.7 -> 45.7 and 30.6 -> 29.7 us against 16
+template <> struct TileT<200>  { static constexpr int T = 32; };  // column seed pass 132 -> 121 us, map 143 -> 124, last pass of a map 126 -> 115 against 16 (its covered columns alone 61 -> 71)
 template <> struct TileT<256>  { static constexpr int T = 8; };
 template <> struct TileT<350>  { static constexpr int T = 32; };  // 14 slots: T * 14 threads must be whole waves
 template <> struct TileT<400>  { static constexpr int T = 8; };
@@ -46,30 +46,32 @@ template <> struct LayerTile<200, kBwdLast, kCol> { static constexpr int T = 32;
 // 400: the column layer passes at 16 vectors (pitch 17: the A-item and
 // B-item reads of a 16-lane group fall in distinct bank pairs; at 8 vectors
 // two B-items share each group's pairs), four-wave workgroups of 55 KB, 8
-// waves per CU against 10; the row passes keep 8 (5-layer training step,
-// batch 500: adjoint column passes 576 -> 485 us and 391 -> 337 us; rows at 16
-// measured slower, 360 -> 380 us forward, and so did every pass at 512)
+// waves per CU against 10 (5-layer training step, batch 500: adjoint column
+// passes 576 -> 485 us and 391 -> 337 us; forward, padded fields only, 320 in
+// 400, batch 100: 68 -> 67)
 template <> struct LayerTile<400, kFwdMid, kCol> { static constexpr int T = 16; };
 template <> struct LayerTile<400, kBwdMid, kCol> { static constexpr int T = 16; };
 template <> struct LayerTile<400, kBwdLast, kCol> { static constexpr int T = 16; };
+// The widths from here on serve padded fields (a field that fills the grid runs
+// these kinds on sep_pass); measured with the aperture at 0.8 of the grid, 5
+// layers, against the size default.
 // 500: the forward passes in one ten-wave workgroup of 32 vectors per CU
 // instead of one five-wave workgroup of 16 (a 68 KB five-wave workgroup
-// leaves no room for a second one on a CU)
+// leaves no room for a second one on a CU): first pass 210 -> 165 us, rows 361
+// -> 304, columns 349 -> 282 (batch 200)
 template <> struct LayerTile<500, kPropOnce, kRow> { static constexpr int T = 32; };
 template <> struct LayerTile<500, kFwdMid, kRow> { static constexpr int T = 32; };
 template <> struct LayerTile<500, kFwdMid, kCol> { static constexpr int T = 32; };
-// 512: the first and the adjoint row passes at 16 vectors (5-layer training
-// step, batch 500: 446 -> 429 and 1113 -> 1077 us, step 11.22 -> 11.11 ms)
+// 512: the adjoint row pass at 16 vectors, 143.5 -> 128 us (batch 64; the first
+// pass is even at 54.5)
 template <> struct LayerTile<512, kPropOnce, kRow> { static constexpr int T = 16; };
 template <> struct LayerTile<512, kBwdMid, kRow> { static constexpr int T = 16; };
+// 1000: first pass 84 -> 71 us, rows 148 -> 123, columns 135 -> 111 (batch 16)
 template <> struct LayerTile<1000, kPropOnce, kRow> { static constexpr int T = 16; };
 template <> struct LayerTile<1000, kFwdMid, kRow> { static constexpr int T = 16; };
 template <> struct LayerTile<1000, kFwdMid, kCol> { static constexpr int T = 16; };
-// (its detector-plane passes measured slower at 16: 185 -> 215 us for the seed
-// pass of a 1000 x 1000 training step, batch 16)
-// (the adjoint passes keep 16: at 32 their registers, capped at 168 for ten
-// waves, spill, and the column pass measured slower; so do the detector-plane
-// passes, which transform only the covered rows and measured slower at 32)
+// (the adjoint passes keep the default: at 32 vectors of 500 and 16 of 1000 their
+// registers, capped at 168 for ten waves, spill)
 
 template <int N, int KIND, int AXIS>
 using LayerCfg = Cfg<std::conditional_t<AXIS == kRow, typename RowPlanFor<N>::type, typename PlanFor<N>::type>,

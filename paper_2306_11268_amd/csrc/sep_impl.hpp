@@ -1,5 +1,7 @@
-// Separable (Fresnel) layer and detector passes on register-resident items, for
-// the longer plans with a layer that fills the grid (slot order, plan.hpp).
+// Separable (Fresnel) layer and detector passes on register-resident items, for a
+// layer that fills the grid (slot order, plan.hpp): the detector-plane rows at
+// every length, the layer passes where they measured faster than the tile
+// passes (sep_kind, launch_impl.hpp).
 //
 // The tile passes of kernels_impl.hpp keep a complex tile of N x T values in
 // shared memory: at 350, 500 and 1000 points 68-104 KB, one workgroup of 5-7
@@ -258,16 +260,13 @@ __device__ __forceinline__ void sep_stage(float2* tab, const float2* __restrict_
 // tables and dphi partials lie as the fields do ([y][x] slots).
 // ---------------------------------------------------------------------------
 // Waves per SIMD asked of the compiler: four (128 registers) for the forward
-// kinds; the adjoint kinds hold two fields and the accumulators: three (168)
-// with A-items of 25 and B-items of at most 32 values, else two.
-template <class G, int KIND>
-constexpr int sep_waves() {
-  constexpr bool acc = KIND == kBwdMid || KIND == kBwdLast;
-  return !acc ? 4 : (!G::SPLIT || G::N1 > 25 || G::N2 * G::IBW > 32 ? 2 : 3);
-}
+// kinds, two (256) for the adjoint kinds, which hold two fields, the next
+// sample's input and the accumulators.
+template <int KIND>
+constexpr int sep_waves() { return KIND == kBwdMid || KIND == kBwdLast ? 2 : 4; }
 
 template <class G, int KIND>
-__global__ void __launch_bounds__(G::P, (sep_waves<G, KIND>())) sep_pass(PassArgs a) {
+__global__ void __launch_bounds__(G::P, sep_waves<KIND>()) sep_pass(PassArgs a) {
   using IT = typename G::IT;
   using PL = typename G::PL;
   constexpr int N = G::N;
@@ -433,7 +432,7 @@ __global__ void __launch_bounds__(G::P, (sep_waves<G, KIND>())) sep_pass(PassArg
 // component at a time where slot order is not natural.
 // ---------------------------------------------------------------------------
 template <class G, int KIND>
-__global__ void __launch_bounds__(G::P, (sep_waves<G, kFwdMid>())) sep_detector_pass(PassArgs a) {
+__global__ void __launch_bounds__(G::P, sep_waves<kFwdMid>()) sep_detector_pass(PassArgs a) {
   using IT = typename G::IT;
   using PL = typename G::PL;
   constexpr int N = G::N;
