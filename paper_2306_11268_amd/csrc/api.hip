@@ -281,8 +281,8 @@ std::string as_name(int N, int kind) {
 // hardware dispatcher then balances them, which measured faster than a
 // persistent schedule with prefetching for them.
 int schedule_layer_pass(int N, lr::PassKind kind, Axis ax, int max_lanes, PassArgs& a) {
-  const int slots = lr::fresnel_pass_slots(N, kind, ax, a.full != 0);
-  const int tile_t = lr::fresnel_pass_tile(N, kind, ax, a.full != 0);
+  const int slots = lr::fresnel_pass_slots(N, kind, ax, a.full ? a.batch : 0);
+  const int tile_t = lr::fresnel_pass_tile(N, kind, ax, a.full ? a.batch : 0);
   if (slots <= 0 || tile_t <= 0) return LR_E_HIP;
   a.ntiles = ceil_div(a.nvec, tile_t);
   if (kind == lr::kBwdMid || kind == lr::kBwdLast) {
@@ -883,7 +883,7 @@ int lr_donn_forward(const lr_donn* net, int32_t batch, const float* d_amp, const
     // pass L+1: rest of hop L+1, detector plane
     if (d_sums || d_intensity || d_field_out) {
       const Axis ax = pass_axis(Lyr + 2);
-      const int tile_t = lr::fresnel_pass_tile(N, lr::kFwdLast, ax, a.full != 0);
+      const int tile_t = lr::fresnel_pass_tile(N, lr::kFwdLast, ax, a.full ? a.batch : 0);
       PassArgs d = a;
       d.ntiles = ceil_div(n, tile_t);
       d.in = a.out;
@@ -1036,7 +1036,7 @@ int lr_donn_backward(const lr_donn* net, int32_t batch, const float* d_phi, cons
       s.grad_int = d_grad_intensity;
       s.grad_sums = gsum;
       s.skip = reinterpret_cast<const float2*>(net->d_skip);
-      const int tile_t = lr::fresnel_pass_tile(N, lr::kBwdFirst, ax, a.full != 0);
+      const int tile_t = lr::fresnel_pass_tile(N, lr::kBwdFirst, ax, a.full ? a.batch : 0);
       s.ntiles = ceil_div(n, tile_t);
       if (gsum) {
         set_detector(s, net->det, L, d_work);

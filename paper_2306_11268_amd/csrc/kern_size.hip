@@ -9,8 +9,8 @@
 
 namespace lr {
 template hipError_t launch_fr_n<LR_FFT_N>(PassKind, Axis, const PassArgs&, hipStream_t);
-template int slots_fr_n<LR_FFT_N>(PassKind, Axis, bool);
-template int tile_fr_n<LR_FFT_N>(PassKind, Axis, bool);
+template int slots_fr_n<LR_FFT_N>(PassKind, Axis, int);
+template int tile_fr_n<LR_FFT_N>(PassKind, Axis, int);
 template hipError_t launch_as_n<LR_FFT_N>(AsPassKind, const PassArgs&, hipStream_t);
 template int as_rows_n<LR_FFT_N>();
 template int slots_as_n<LR_FFT_N>(AsPassKind, bool);

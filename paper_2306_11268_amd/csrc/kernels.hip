@@ -8,8 +8,8 @@ namespace lr {
 
 // Per-size entry points, defined in kern_size.hip (one object per size).
 template <int N> hipError_t launch_fr_n(PassKind, Axis, const PassArgs&, hipStream_t);
-template <int N> int slots_fr_n(PassKind, Axis, bool);
-template <int N> int tile_fr_n(PassKind, Axis, bool);
+template <int N> int slots_fr_n(PassKind, Axis, int);
+template <int N> int tile_fr_n(PassKind, Axis, int);
 template <int N> hipError_t launch_as_n(AsPassKind, const PassArgs&, hipStream_t);
 template <int N> int as_rows_n();
 template <int N> int slots_as_n(AsPassKind, bool);
@@ -548,7 +548,7 @@ hipError_t launch_fresnel_pass(int N, PassKind kind, Axis axis, const PassArgs& 
   }
 }
 
-int fresnel_pass_tile(int N, PassKind kind, Axis axis, bool full) {
+int fresnel_pass_tile(int N, PassKind kind, Axis axis, int full) {
   switch (N) {
     case 64: return tile_fr_n<64>(kind, axis, full);
     case 100: return tile_fr_n<100>(kind, axis, full);
@@ -565,7 +565,7 @@ int fresnel_pass_tile(int N, PassKind kind, Axis axis, bool full) {
   }
 }
 
-int fresnel_pass_slots(int N, PassKind kind, Axis axis, bool full) {
+int fresnel_pass_slots(int N, PassKind kind, Axis axis, int full) {
   switch (N) {
     case 64: return slots_fr_n<64>(kind, axis, full);
     case 100: return slots_fr_n<100>(kind, axis, full);

@@ -59,7 +59,7 @@ struct PassArgs {
   // transfer function H[ky][kx] (angular-spectrum path)
   const float2* tab;
   int conj_tab;
-  float scale;    // angular-spectrum column pass: factor of its output, 1/N^2
+  float scale;    // angular-spectrum column pass: factor of its output, 1/N^2 (where its inverse roots do not carry it)
   // modulation gamma*exp(j*phi_l), oriented [q][vec] (separable path) or natural [y][x]
   const float2* mod;
   int conj_mod;
@@ -178,9 +178,10 @@ TileShape tile_shape(int N, int axis);
 
 hipError_t launch_fresnel_pass(int N, PassKind kind, Axis axis, const PassArgs& a, hipStream_t st);
 // Workgroups of a separable pass kernel that fit on the current device at
-// once, and the vectors each of its workgroups transforms.
-int fresnel_pass_slots(int N, PassKind kind, Axis axis, bool full);
-int fresnel_pass_tile(int N, PassKind kind, Axis axis, bool full);
+// once, and the vectors each of its workgroups transforms (full: samples of a
+// call on a slot-ordered field, 0 for a padded one).
+int fresnel_pass_slots(int N, PassKind kind, Axis axis, int full);
+int fresnel_pass_tile(int N, PassKind kind, Axis axis, int full);
 // Angular-spectrum passes: row kinds run PassArgs::workers workgroups over
 // PassArgs::ntiles tiles of as_row_tile(N) rows; column kinds set both
 // themselves.  as_pass_slots: workgroups of an accumulating row kind that fit

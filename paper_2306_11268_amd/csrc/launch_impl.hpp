@@ -130,17 +130,50 @@ struct SepFor {
                                   Sep<PL, kCol, (PL::N2 <= 32 ? 256 : 512) / PL::N2, ACC, !ACC>>;
 };
 
+// The column kinds take the tile passes where a batch leaves the CUs fewer than
+// two register workgroups each (12-64 columns each, against 8-32): at half of
+// that and below they measured 5-30% slower (100 points, 16 samples, forward 11.5
+// us on tiles, 13.7; 256, 8 samples, 11.1 and 12.5, adjoint 15.1 and 16.8; 512, 8
+// samples, 22.6 and 24.9, last adjoint 32.6 and 41.8; 1000, 4 samples, 36.8 and
+// 43.4).  Forward at 350 and 500 points, where a tile is alone on its CU, the
+// register passes are even from one sample on; the adjoint ones at 500 are
+// slower up to about 28 samples (16: 60 and 70) and, the last, 128 (64: 145 and
+// 154).  At 512 the adjoint layer pass is the slower one again past 128 samples
+// (256: 809 and 833, 500: 1536 and 1652).
+template <int N, int KIND, int AXIS>
+bool use_sep(int batch) {
+  if constexpr (!sep_kind<N, KIND, AXIS>()) {
+    return false;
+  } else if constexpr (AXIS == kRow) {
+    return true;
+  } else {
+    constexpr int T = SepFor<N, KIND, AXIS>::type::T;
+    constexpr bool ACC = KIND == kBwdMid || KIND == kBwdLast;
+    constexpr int least = !ACC && (N == 350 || N == 500) ? 0 : N == 500 ? (KIND == kBwdLast ? 21 : 5) : 2;  // per CU
+    const long long groups = (long long)((N + T - 1) / T) * batch;
+    if (N == 512 && KIND == kBwdMid && groups > 16ll * device_cus()) return false;
+    return groups >= (long long)least * device_cus();
+  }
+}
+
+// FULL: a slot-ordered field.
 template <int N, int KIND, int AXIS, bool FULL>
 hipError_t launch_fr(const PassArgs& a, hipStream_t st) {
   if constexpr (FULL && sep_kind<N, KIND, AXIS>()) {
-    using G = typename SepFor<N, KIND, AXIS>::type;
-    if constexpr (KIND == kFwdLast || KIND == kBwdFirst) {
-      if (a.ntiles < 1 || a.batch < 1) return hipErrorInvalidValue;
-      hipLaunchKernelGGL((sep_detector_pass<G, KIND>), dim3(a.ntiles * a.batch), dim3(G::P), 0, st, a);
-    } else {
-      if (a.workers < 1 || (KIND == kPropOnce && !a.in_real)) return hipErrorInvalidValue;
-      hipLaunchKernelGGL((sep_pass<G, KIND>), dim3(8 * ((a.workers + 7) / 8)), dim3(G::P), 0, st, a);
+    if (use_sep<N, KIND, AXIS>(a.batch)) {
+      using G = typename SepFor<N, KIND, AXIS>::type;
+      if constexpr (KIND == kFwdLast || KIND == kBwdFirst) {
+        if (a.ntiles < 1 || a.batch < 1) return hipErrorInvalidValue;
+        hipLaunchKernelGGL((sep_detector_pass<G, KIND>), dim3(a.ntiles * a.batch), dim3(G::P), 0, st, a);
+      } else {
+        if (a.workers < 1 || (KIND == kPropOnce && !a.in_real)) return hipErrorInvalidValue;
+        hipLaunchKernelGGL((sep_pass<G, KIND>), dim3(8 * ((a.workers + 7) / 8)), dim3(G::P), 0, st, a);
+      }
+      return hipGetLastError();
     }
+  }
+  if constexpr (FULL && AXIS == kRow && sep_kind<N, KIND, AXIS>()) {
+    return hipErrorInvalidValue;  // (row kinds have no second variant)
   } else if constexpr (FULL && wave_tile_kind<N, KIND, AXIS>()) {
     if (a.workers < 1) return hipErrorInvalidValue;
     const dim3 grid(8 * ((a.workers + 7) / 8));
@@ -158,13 +191,24 @@ hipError_t launch_fr(const PassArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <int N, int KIND, int AXIS, bool FULL>
-int slots_fr() {
+template <int N, int KIND, int AXIS>
+int slots_sep() {
   static int per_cu = 0;
   if (per_cu == 0) {
-    if constexpr (FULL && sep_kind<N, KIND, AXIS>()) {
-      using G = typename SepFor<N, KIND, AXIS>::type;
-      per_cu = resident_per_cu(reinterpret_cast<const void*>(&sep_pass<G, KIND>), G::P);
+    using G = typename SepFor<N, KIND, AXIS>::type;
+    per_cu = resident_per_cu(reinterpret_cast<const void*>(&sep_pass<G, KIND>), G::P);
+  }
+  return per_cu * device_cus();
+}
+template <int N, int KIND, int AXIS, bool FULL>
+int slots_fr(int full) {
+  if constexpr (FULL && sep_kind<N, KIND, AXIS>()) {
+    if (use_sep<N, KIND, AXIS>(full)) return slots_sep<N, KIND, AXIS>();
+  }
+  static int per_cu = 0;
+  if (per_cu == 0) {
+    if constexpr (FULL && AXIS == kRow && sep_kind<N, KIND, AXIS>()) {
+      return 0;
     } else if constexpr (FULL && wave_tile_kind<N, KIND, AXIS>()) {
       per_cu = resident_per_cu(reinterpret_cast<const void*>(&wave_pass<typename PlanFor<N>::type, KIND, AXIS>), 64);
     } else {
@@ -176,27 +220,28 @@ int slots_fr() {
 }
 
 template <int N, int KIND>
-int slots_fr_axis(Axis axis, bool full) {
-  if (full) return axis == kRow ? slots_fr<N, KIND, kRow, true>() : slots_fr<N, KIND, kCol, true>();
-  return axis == kRow ? slots_fr<N, KIND, kRow, false>() : slots_fr<N, KIND, kCol, false>();
+int slots_fr_axis(Axis axis, int full) {
+  if (full) return axis == kRow ? slots_fr<N, KIND, kRow, true>(full) : slots_fr<N, KIND, kCol, true>(full);
+  return axis == kRow ? slots_fr<N, KIND, kRow, false>(0) : slots_fr<N, KIND, kCol, false>(0);
 }
 
 template <int N, int KIND>
-int tile_fr_axis(Axis axis, bool full) {
+int tile_fr_axis(Axis axis, int full) {
   if constexpr (sep_kind<N, KIND, kRow>()) {
     if (axis == kRow && full) return SepFor<N, KIND, kRow>::type::T;
   }
   if constexpr (sep_kind<N, KIND, kCol>()) {
-    if (axis == kCol && full) return SepFor<N, KIND, kCol>::type::T;
+    if (axis == kCol && full && use_sep<N, KIND, kCol>(full)) return SepFor<N, KIND, kCol>::type::T;
   }
   if constexpr (KIND == kFwdLast || KIND == kBwdFirst) return TileT<N>::T;
   if (axis == kRow) return full && wave_tile_kind<N, KIND, kRow>() ? 8 : LayerTile<N, KIND, kRow>::T;
   return full && wave_tile_kind<N, KIND, kCol>() ? 8 : LayerTile<N, KIND, kCol>::T;
 }
 
-// Vectors per workgroup of a separable pass.
+// Vectors per workgroup of a separable pass (full: samples of a call on a
+// slot-ordered field, 0 for a padded one).
 template <int N>
-int tile_fr_n(PassKind kind, Axis axis, bool full) {
+int tile_fr_n(PassKind kind, Axis axis, int full) {
   switch (kind) {
     case kPropOnce: return tile_fr_axis<N, kPropOnce>(axis, full);
     case kFwdMid: return tile_fr_axis<N, kFwdMid>(axis, full);
@@ -209,7 +254,7 @@ int tile_fr_n(PassKind kind, Axis axis, bool full) {
 }
 
 template <int N>
-int slots_fr_n(PassKind kind, Axis axis, bool full) {
+int slots_fr_n(PassKind kind, Axis axis, int full) {
   switch (kind) {
     case kPropOnce: return slots_fr_axis<N, kPropOnce>(axis, full);
     case kFwdMid: return slots_fr_axis<N, kFwdMid>(axis, full);

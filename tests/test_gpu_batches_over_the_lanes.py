@@ -36,8 +36,8 @@ def hop(u, h, n, m):
     return torch.fft.ifft2(torch.fft.fft2(p) * h)[:, o:o + n, o:o + n]
 
 
-def check(lrb, approx, optics, n, m, layers, seed):
-    b = BATCH[m]
+def check(lrb, approx, optics, n, m, layers, seed, b=0):
+    b = b or BATCH[m]
     print(f"approx {approx} n {n} m {m} layers {layers} batch {b}", flush=True)
     g = torch.Generator(device="cuda")
     g.manual_seed(1000 * m + n)
@@ -94,3 +94,11 @@ def test_angular_spectrum(lrb, m, half):
 def test_sampled_kernel(lrb, m):
     n = m // 2 - (m // 2 - m) % 2
     check(lrb, lrb.LR_RS_IR, INFRARED, n, m, 1, "map")
+
+
+# (the column passes change kernels between the two batches of a pair, on 256 CUs)
+@pytest.mark.parametrize("m,b", [(64, 255), (64, 256), (100, 255), (100, 256), (128, 127), (128, 128), (256, 31),
+                                 (256, 32), (400, 20), (400, 21), (500, 30), (500, 31), (500, 127), (500, 128),
+                                 (512, 15), (512, 16), (512, 128), (512, 129), (1000, 6), (1000, 7)])
+def test_both_sides_of_the_batch_rule(lrb, m, b):
+    check(lrb, lrb.LR_FRESNEL, VISIBLE, m, m, 3, "map", b)
