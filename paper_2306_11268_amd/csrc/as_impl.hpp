@@ -104,12 +104,19 @@ struct AsRows : AsItems<PL> {
   // registers, one less for the 40-value items and for the accumulating kinds
   static constexpr int WAVES = IT::N2 * IT::IB > 32 ? 3 : 4;
   static constexpr int WAVES_ACC = WAVES - 1;
+  // and two for the middle backward kind of the Good-Thomas plan: its reordered
+  // items, the accumulators and a second transform do not fit in three waves'
+  // 168 registers (350x350: 36 us at three, 24 at two with a batch of 16; 94
+  // and 67 with 64). The last layer's kind has one transform and keeps three
+  // (54 and 62 us with 64).
+  static constexpr int WAVES_MID = PL::PFA ? 2 : WAVES_ACC;
   static_assert(R * PR * (SPLIT ? 4 : 8) + R * kMaxRegions * 4 < 64 * 1024, "static shared memory");
 };
 
 template <class PL, int KIND, bool HALF>
-__global__ void __launch_bounds__(AsRows<PL>::P, (KIND == kAsRowBwdMid || KIND == kAsRowBwdLast)
-                                                     ? AsRows<PL>::WAVES_ACC : AsRows<PL>::WAVES)
+__global__ void __launch_bounds__(AsRows<PL>::P, KIND == kAsRowBwdMid    ? AsRows<PL>::WAVES_MID
+                                                 : KIND == kAsRowBwdLast ? AsRows<PL>::WAVES_ACC
+                                                                         : AsRows<PL>::WAVES)
     as_row_pass(PassArgs a) {
   using W = AsRows<PL>;
   using IT = AsItems<PL, KIND == kAsRowBwdMid || KIND == kAsRowBwdLast>;
