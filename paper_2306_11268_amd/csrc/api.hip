@@ -186,7 +186,7 @@ Layout make_layout(const lr_donn* net, int batch, int op) {
   const int N = net->n_fft;
   const bool as = net->approx != LR_FRESNEL;  // the non-separable passes
   const int tiles = ceil_div(n, lr::tile_shape(N, 0).T);
-  L.ntiles_vec = as ? ceil_div(n, lr::as_row_tile(N)) : tiles;
+  L.ntiles_vec = as ? ceil_div(n, lr::as_row_tile(N, net->approx == LR_FRAUNHOFER)) : tiles;
   const size_t c64 = 8;
   const size_t nn = static_cast<size_t>(n) * n;
   const size_t field = static_cast<size_t>(batch) * (as ? static_cast<size_t>(n) * N : nn) * c64;
@@ -319,7 +319,7 @@ int fr_pass(int N, lr::PassKind kind, Axis ax, const PassArgs& a, hipStream_t st
 // (accumulating kinds, max_lanes > 0) as many persistent ones as fit, each
 // keeping one tile; a.lanes returns the partials written.
 int schedule_as_row(int N, lr::AsPassKind kind, int max_lanes, PassArgs& a) {
-  const int tile = lr::as_row_tile(N);
+  const int tile = lr::as_row_tile(N, a.spec_centred != 0);
   if (tile <= 0) return LR_E_HIP;
   a.ntiles = ceil_div(a.n, tile);
   a.lanes = 0;

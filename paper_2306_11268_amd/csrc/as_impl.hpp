@@ -619,45 +619,56 @@ __global__ void __launch_bounds__((AsCols<PL, T>::P), (AsCols<PL, T>::WAVES)) as
 // on 128-byte lines, as many as fill 256 lanes (a five-wave workgroup leaves
 // SIMDs uneven, sep_impl.hpp): 200 points 48 -> 41 us for 200 samples, 250 in
 // 500 47 -> 37 us for 32 (at 400, whose rows do, 45 -> 54 us, so not there).
-template <int N> struct AsColT { static constexpr int T = 16; };
-template <> struct AsColT<100> { static constexpr int T = 25; };
-template <> struct AsColT<200> { static constexpr int T = 25; };
-template <> struct AsColT<350> { static constexpr int T = 32; };
-template <> struct AsColT<500> { static constexpr int T = 12; };
+// Far field of 100 and 200: whole waves.
+template <int N, bool FAR> struct AsColT { static constexpr int T = 16; };
+template <> struct AsColT<100, false> { static constexpr int T = 25; };
+template <> struct AsColT<200, false> { static constexpr int T = 25; };
+template <> struct AsColT<100, true> { static constexpr int T = 32; };
+template <> struct AsColT<200, true> { static constexpr int T = 32; };
+template <bool FAR> struct AsColT<350, FAR> { static constexpr int T = 32; };
+template <bool FAR> struct AsColT<500, FAR> { static constexpr int T = 12; };
+
+template <int N, bool FAR>
+using AsPlan = typename std::conditional_t<FAR, FarPlanFor<N>, AsPlanFor<N>>::type;
 
 // n = N/2 centred and N1 divisible by 4: HalfDft.  Its roots add 2-4% to the
 // rounding of a transform at 20 values, where a whole transform has none
 // (Good-Thomas 4 x 5).  A hop at 400 makes up for it (ScaledRoots; 1.94e-7 before
 // half transforms, 1.92e-7 now, against 64 bits), one at 200 does not (1.77e-7
-// -> 1.83e-7), nor does the far field at 400 (1.33e-7 -> 1.36e-7).  These take whole
-// transforms: 100 in 200, 5 layers, batch 200, 263 -> 287 us; far field of 200 in
-// 400, batch 64, 38.6 -> 41.3 us.
-template <int N>
-constexpr bool as_half_plan() { return AsPlanFor<N>::type::N1 % 4 == 0 && N != 200; }
-template <int N>
-bool as_half(const PassArgs& a, bool far) {
-  return as_half_plan<N>() && 2 * a.n == N && 4 * a.off == N && !(far && N == 400);
+// -> 1.83e-7) and takes whole transforms: 100 in 200, 5 layers, batch 200, 263 ->
+// 287 us.
+template <int N, bool FAR = false>
+constexpr bool as_half_plan() { return AsPlan<N, FAR>::N1 % 4 == 0 && N != 200; }
+template <int N, bool FAR>
+bool as_half(const PassArgs& a) {
+  return as_half_plan<N, FAR>() && 2 * a.n == N && 4 * a.off == N;
 }
 
-template <int N, int KIND, bool HALF>
-hipError_t launch_as_row(const PassArgs& a, hipStream_t st) {
-  using PL = typename AsPlanFor<N>::type;
-  hipLaunchKernelGGL((as_row_pass<PL, KIND, HALF>), dim3(a.workers), dim3(AsRows<PL>::P), 0, st, a);
+template <int N, int KIND, bool FAR>
+hipError_t launch_as_rows(const PassArgs& a, hipStream_t st) {
+  using PL = AsPlan<N, FAR>;
+  if constexpr (as_half_plan<N, FAR>()) {
+    if (as_half<N, FAR>(a)) {
+      hipLaunchKernelGGL((as_row_pass<PL, KIND, true>), dim3(a.workers), dim3(AsRows<PL>::P), 0, st, a);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((as_row_pass<PL, KIND, false>), dim3(a.workers), dim3(AsRows<PL>::P), 0, st, a);
   return hipGetLastError();
 }
 template <int N, int KIND>
 hipError_t launch_as_row(const PassArgs& a, hipStream_t st) {
   if (a.workers < 1 || a.n < 1 || a.n > N || a.off != (N - a.n) / 2) return hipErrorInvalidValue;
-  if constexpr (as_half_plan<N>()) {
-    if (as_half<N>(a, a.spec_centred != 0)) return launch_as_row<N, KIND, true>(a, st);
+  if constexpr (KIND == kAsRowFirst) {
+    if (a.spec_centred) return launch_as_rows<N, KIND, true>(a, st);
   }
-  return launch_as_row<N, KIND, false>(a, st);
+  return launch_as_rows<N, KIND, false>(a, st);
 }
 
 template <int N, bool FAR, bool HALF>
 hipError_t launch_as_cols(const PassArgs& args, hipStream_t st) {
-  using PL = typename AsPlanFor<N>::type;
-  constexpr int T = AsColT<N>::T;
+  using PL = AsPlan<N, FAR>;
+  constexpr int T = AsColT<N, FAR>::T;
   constexpr int P = AsCols<PL, T>::P;
   constexpr int tiles = (N + T - 1) / T;
   // a launch holds fewer than 2^32 threads: batches past that (of apertures a
@@ -679,8 +690,8 @@ hipError_t launch_as_cols(const PassArgs& args, hipStream_t st) {
 template <int N, bool FAR>
 hipError_t launch_as_col(const PassArgs& a, hipStream_t st) {
   if (a.batch < 1 || a.n < 1 || a.n > N || a.off != (N - a.n) / 2) return hipErrorInvalidValue;
-  if constexpr (as_half_plan<N>()) {
-    if (as_half<N>(a, FAR)) return launch_as_cols<N, FAR, true>(a, st);
+  if constexpr (as_half_plan<N, FAR>()) {
+    if (as_half<N, FAR>(a)) return launch_as_cols<N, FAR, true>(a, st);
   }
   return launch_as_cols<N, FAR, false>(a, st);
 }
@@ -703,10 +714,10 @@ hipError_t launch_as_n(AsPassKind kind, const PassArgs& a, hipStream_t st) {
 
 // Rows per workgroup, and resident workgroups of an accumulating row kind.
 template <int N>
-int as_rows_n() { return AsRows<typename AsPlanFor<N>::type>::R; }
+int as_rows_n(bool far) { return far ? AsRows<AsPlan<N, true>>::R : AsRows<AsPlan<N, false>>::R; }
 template <int N>
 int slots_as_n(AsPassKind kind, bool half) {
-  using PL = typename AsPlanFor<N>::type;
+  using PL = AsPlan<N, false>;
   static int cache[2][2] = {};
   const int m = kind == kAsRowBwdMid ? 0 : 1;
   int& c = cache[m][half ? 1 : 0];

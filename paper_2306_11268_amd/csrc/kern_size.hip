@@ -12,7 +12,7 @@ template hipError_t launch_fr_n<LR_FFT_N>(PassKind, Axis, const PassArgs&, hipSt
 template int slots_fr_n<LR_FFT_N>(PassKind, Axis, int);
 template int tile_fr_n<LR_FFT_N>(PassKind, Axis, int);
 template hipError_t launch_as_n<LR_FFT_N>(AsPassKind, const PassArgs&, hipStream_t);
-template int as_rows_n<LR_FFT_N>();
+template int as_rows_n<LR_FFT_N>(bool);
 template int slots_as_n<LR_FFT_N>(AsPassKind, bool);
 template TileShape shape_n<LR_FFT_N>();
 template bool row_major_n<LR_FFT_N>(bool);

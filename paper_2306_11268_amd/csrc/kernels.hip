@@ -11,7 +11,7 @@ template <int N> hipError_t launch_fr_n(PassKind, Axis, const PassArgs&, hipStre
 template <int N> int slots_fr_n(PassKind, Axis, int);
 template <int N> int tile_fr_n(PassKind, Axis, int);
 template <int N> hipError_t launch_as_n(AsPassKind, const PassArgs&, hipStream_t);
-template <int N> int as_rows_n();
+template <int N> int as_rows_n(bool);
 template <int N> int slots_as_n(AsPassKind, bool);
 template <int N> TileShape shape_n();
 template <int N> SlotMap slot_map_n();
@@ -600,19 +600,19 @@ hipError_t launch_as_pass(int N, AsPassKind kind, const PassArgs& a, hipStream_t
 }
 
 
-int as_row_tile(int N) {
+int as_row_tile(int N, bool far) {
   switch (N) {
-    case 64: return as_rows_n<64>();
-    case 100: return as_rows_n<100>();
-    case 128: return as_rows_n<128>();
-    case 200: return as_rows_n<200>();
-    case 256: return as_rows_n<256>();
-    case 350: return as_rows_n<350>();
-    case 400: return as_rows_n<400>();
-    case 500: return as_rows_n<500>();
-    case 512: return as_rows_n<512>();
-    case 1000: return as_rows_n<1000>();
-    case 1024: return as_rows_n<1024>();
+    case 64: return as_rows_n<64>(far);
+    case 100: return as_rows_n<100>(far);
+    case 128: return as_rows_n<128>(far);
+    case 200: return as_rows_n<200>(far);
+    case 256: return as_rows_n<256>(far);
+    case 350: return as_rows_n<350>(far);
+    case 400: return as_rows_n<400>(far);
+    case 500: return as_rows_n<500>(far);
+    case 512: return as_rows_n<512>(far);
+    case 1000: return as_rows_n<1000>(far);
+    case 1024: return as_rows_n<1024>(far);
     default: return 0;
   }
 }

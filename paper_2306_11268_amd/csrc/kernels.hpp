@@ -187,7 +187,7 @@ int fresnel_pass_tile(int N, PassKind kind, Axis axis, int full);
 // themselves.  as_pass_slots: workgroups of an accumulating row kind that fit
 // on the device at once (half: the aperture is the middle half of the grid).
 hipError_t launch_as_pass(int N, AsPassKind kind, const PassArgs& a, hipStream_t st);
-int as_row_tile(int N);
+int as_row_tile(int N, bool far);
 int as_pass_slots(int N, AsPassKind kind, bool half);
 
 // Small helper kernels.
