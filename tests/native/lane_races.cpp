@@ -157,8 +157,8 @@ bool as_rows() {
 }
 template <bool HALF, bool FAR>
 bool as_col() {
-  using PL = typename AsPlanFor<N>::type;
-  constexpr int T = AsColT<N>::T;
+  using PL = AsPlan<N, FAR>;
+  constexpr int T = AsColT<N, FAR>::T;
   const int tiles = (N + T - 1) / T;
   return run(FAR ? "as far" : "as col", &as_col_pass<PL, T, HALF, FAR>, AsCols<PL, T>::P, (tiles * 3 + 7) / 8 * 8,
              args(HALF ? N / 2 : N, tiles, tiles * 3));
@@ -183,7 +183,8 @@ bool sep(const char* what) {
 
 int main() {
   bool ok = as_rows<false>() & as_col<false, false>() & as_col<false, true>();
-  if constexpr (as_half_plan<N>()) ok &= as_rows<true>() & as_col<true, false>() & as_col<true, true>();
+  if constexpr (as_half_plan<N>()) ok &= as_rows<true>() & as_col<true, false>();
+  if constexpr (as_half_plan<N, true>()) ok &= as_col<true, true>();
   ok &= sep<kPropOnce, kRow>("sep first row") & sep<kFwdMid, kRow>("sep mid row") & sep<kBwdMid, kRow>("sep bwd row") &
         sep<kFwdLast, kRow>("sep last row") & sep<kBwdFirst, kRow>("sep seed row") &
         sep<kFwdMid, kCol>("sep mid col") & sep<kBwdMid, kCol>("sep bwd col") & sep<kBwdLast, kCol>("sep bwd last col");
